@@ -1,5 +1,6 @@
 // Host side of the C ABI: argument checks, layer ownership, launch-order row binning.
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -19,8 +20,7 @@ hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 void free_layer_buffers(LayerDev& d) {
     void* ptrs[] = {d.sign, d.signT, d.perm, d.row_ptr, d.col_idx, d.val, d.rowsum, d.chunk_ptr, d.slot_valsum, d.vald, d.signC,
-                    d.seg_ptr, d.ent, d.rows_perm, d.rows_blk, d.rows_ek, d.rows_ev, d.rows_sign, d.rows_valsum,
-                    d.rowsw_perm, d.rowsw_blk, d.rowsw_ek, d.rowsw_ev, d.rowsw_sign, d.rowsw_valsum};
+                    d.seg_ptr, d.ent, d.rows_sign, d.rows_first, d.rows_count, d.rows_step, d.rows_valsum};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     d = LayerDev{};
@@ -110,46 +110,113 @@ void build_tile_runs(const std::vector<int32_t>& perm, const std::vector<int32_t
     }
 }
 
-// Row lists for the rows-in-lanes kernel (see LayerDev): rows in order of decreasing residual count, so
-// that the 64 rows of a block have nearly the same number of steps; a block takes as many steps as its
-// longest row, shorter rows are padded with (offset 0, value 0).
-void build_row_lists(const std::vector<int32_t>& row_ptr, const std::vector<int32_t>& col, const std::vector<float>& val,
-                     std::vector<int32_t>& perm, std::vector<int32_t>& blk, std::vector<uint32_t>& ek,
-                     std::vector<double>& ev, std::vector<double>& valsum, int group_rows) {
-    // group_rows: rows are sorted by length inside groups of that many consecutive rows (a multiple of 64; every
-    // group but the last fills whole blocks), or over the whole layer (0)
-    const int N = (int)row_ptr.size() - 1;
-    const int nb = (N + kWave - 1) / kWave, Nr = nb * kWave;
-    const int G = group_rows > 0 ? group_rows : std::max(N, 1);
-    perm.assign(Nr, -1);
-    for (int g0 = 0; g0 < N; g0 += G) {
-        const int g1 = std::min(N, g0 + G);
-        std::iota(perm.begin() + g0, perm.begin() + g1, g0);
-        std::stable_sort(perm.begin() + g0, perm.begin() + g1, [&](int a, int b) {
-            return row_ptr[a + 1] - row_ptr[a] > row_ptr[b + 1] - row_ptr[b];
-        });
-    }
-    blk.assign(nb + 1, 0);
-    for (int b = 0; b < nb; ++b) {
-        const int n0 = perm[(size_t)b * kWave];                    // longest row of the block (its first slot is a row)
-        blk[b + 1] = blk[b] + (row_ptr[n0 + 1] - row_ptr[n0]);
-    }
-    ek.assign((size_t)blk[nb] * kWave, 0u);
-    ev.assign((size_t)blk[nb] * kWave, 0.0);
-    valsum.assign(Nr, 0.0);
-    for (int i = 0; i < Nr; ++i) {
-        const int n = perm[i];
-        if (n < 0) continue;
-        const int b = i / kWave, lane = i % kWave;
-        double sum = 0.0;
+// Digit steps of the matrix-core forward kernel (see LayerDev and kStepBytes).
+struct DigitSteps {
+    int windows = 1;
+    std::vector<int32_t> first;
+    std::vector<uint8_t> count;
+    std::vector<uint8_t> step;
+    std::vector<double> valsum;
+    int unit = 0;
+};
+void build_digit_steps(int N, const std::vector<int32_t>& row_ptr, const std::vector<int32_t>& col, const std::vector<float>& val,
+                       bool bytes, DigitSteps& o) {
+    const int tiles = 2 * ((N + 31) / 32), rows = 16 * tiles;
+    int lo = 0, hi = -1;
+    bool any = false;
+    o.valsum.assign(rows, 0.0);
+    for (int n = 0; n < N; ++n)
         for (int e = row_ptr[n]; e < row_ptr[n + 1]; ++e) {
-            const size_t at = ((size_t)blk[b] + (e - row_ptr[n])) * kWave + lane;
-            ek[at] = (uint32_t)col[e] * kRowsRowBytes;
-            ev[at] = std::ldexp((double)val[e], kEntValScaleLog2);
-            sum += (double)val[e];
+            o.valsum[n] += (double)val[e];
+            const float v = std::fabs(val[e]);
+            if (!(v > 0.0f) || std::isinf(v)) continue;
+            int ex;
+            const double f = std::frexp((double)v, &ex);           // v = f * 2^ex, f in [.5, 1)
+            uint32_t mant = (uint32_t)(f * 16777216.0);            // 24 bits
+            int low = ex - 24;
+            while (!(mant & 1u)) { mant >>= 1; ++low; }
+            if (!any || low < lo) lo = low;
+            if (!any || ex - 1 > hi) hi = ex - 1;
+            any = true;
         }
-        valsum[i] = sum;
+    o.windows = any ? (hi - lo + 2 + kWindowBits - 1) / kWindowBits : 1;
+    o.unit = lo;
+    const int W = o.windows;
+    o.first.assign(tiles + 1, 0);
+    o.count.assign((size_t)tiles * 2 * W, 1);
+    long long steps = 0;
+    struct Entry { int k; int q[2]; };
+    for (int quad = 0; quad < 2 * tiles; ++quad) {
+        if (quad % 2 == 0) o.first[quad / 2] = (int32_t)steps;
+        for (int w = 0; w < W; ++w) {
+            std::vector<Entry> lists[4];
+            size_t longest = 0;
+            for (int pr = 0; pr < 4; ++pr) {
+                const int ra = 16 * (quad / 2) + 2 * (quad % 2) + pr / 2 + 4 * (pr % 2), rb = ra + 8;
+                std::vector<Entry>& list = lists[pr];
+                int ea = ra < N ? row_ptr[ra] : 0, eb = rb < N ? row_ptr[rb] : 0;
+                const int eae = ra < N ? row_ptr[ra + 1] : 0, ebe = rb < N ? row_ptr[rb + 1] : 0;
+                auto digits_of = [&](float v) -> int {
+                    if (!std::isfinite(v)) v = 0.0f;
+                    double x = std::ldexp((double)v, -lo);
+                    int q = 0;
+                    for (int ww = W - 1; ww >= w; --ww) {
+                        const double qd = std::rint(std::ldexp(x, -kWindowBits * ww));
+                        x -= std::ldexp(qd, kWindowBits * ww);
+                        q = (int)qd;
+                    }
+                    return q;
+                };
+                while (ea < eae || eb < ebe) {
+                    const int ka = ea < eae ? col[ea] : INT_MAX, kb = eb < ebe ? col[eb] : INT_MAX, k = std::min(ka, kb);
+                    Entry x{k, {0, 0}};
+                    if (ka == k) x.q[0] = digits_of(val[ea++]);
+                    if (kb == k) x.q[1] = digits_of(val[eb++]);
+                    if (W == 1 || x.q[0] || x.q[1]) list.push_back(x);
+                }
+                longest = std::max(longest, list.size());
+            }
+            const int S = digit_steps_of((int)longest);
+            o.count[(size_t)quad * W + w] = (uint8_t)S;
+            for (int pr = 0; pr < 4; ++pr) {
+                    std::vector<Entry>& list = lists[pr];
+                    o.step.resize((size_t)(steps + S) * kStepBytes, 0);
+                    uint8_t* base = &o.step[(size_t)steps * kStepBytes];
+                    std::stable_sort(list.begin(), list.end(), [](const Entry& a, const Entry& b) { return (a.k & 31) < (b.k & 31); });
+                    for (int gam = 0; gam < 4 * S; ++gam) {         // a half wave's 32 rows of one gather
+                        uint8_t* st = base + (size_t)(gam >> 2) * kStepBytes;
+                        const int half = (gam >> 1) & 1, qq = gam & 1;
+                        const int k_first = gam < (int)list.size() ? list[gam].k : 0;
+                        for (int sl = 0; sl < 32; ++sl) {
+                            const size_t e = (size_t)sl * 4 * S + gam;
+                            const int g = 2 * half + (sl >> 4), i = sl & 15, tt = 16 * qq + i;
+                            const Entry x = e < list.size() ? list[e] : Entry{k_first, {0, 0}};
+                            uint16_t kk = (uint16_t)(bytes ? x.k * 8 : x.k);
+                            std::memcpy(st + kStepRows + (16 * g + i) * 4 + 2 * qq, &kk, 2);
+                            for (int hh = 0; hh < 2; ++hh) {
+                                int q = x.q[hh];
+                                for (int d = 0; d < 6; ++d) {
+                                    const int dg = d == 5 ? q : ((q + 16) & 31) - 16;
+                                    q = (q - dg) >> 5;
+                                    const uint32_t m = (uint32_t)std::abs(dg);
+                                    const uint32_t code = ((x.k & 1) == 0 ? m : m < 8 ? 2 * m : m + 8) | (dg < 0 ? 32u : 0u);
+                                    const int frag = g * 12 + hh * 6 + d;
+                                    for (int bit = 0; bit < 6; ++bit)
+                                        if ((code >> bit) & 1u) {
+                                            const int at = 6 * tt + bit;          // bit of the 192
+                                            uint8_t* p = at < 128 ? st + frag * 16 + at / 8 : st + kStepA8 + frag * 8 + (at - 128) / 8;
+                                            *p |= (uint8_t)(1u << (at & 7));
+                                        }
+                                }
+                            }
+                        }
+                    }
+                    steps += S;
+            }
+        }
     }
+    o.first[tiles] = (int32_t)steps;
+    o.step.resize((size_t)(steps + kStepPad) * kStepBytes, 0);
 }
 
 int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStream_t s, LayerDev& d) {
@@ -250,71 +317,39 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
     APB_HIP(hipMemcpyAsync(d.seg_ptr, hseg.data(), hseg.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     if (!hent.empty())
         APB_HIP(hipMemcpyAsync(d.ent, hent.data(), hent.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-    // Row lists for the rows-in-lanes kernel: only where K fits its on-chip code table and rows carry
-    // enough residuals for the padding of the lists (to the longest row of each block of 64) to stay small.
-    std::vector<int32_t> rperm, rblk;
-    // The sign words of a block of 64 slots are stored in the order the matrix tiles take them: the kernel's lane
-    // i (of 16) owns slots i, 16 + i, 32 + i, 48 + i of the block -- row i of its four tiles -- and finds their
-    // words of one word row side by side, position 4 * i + t: one 16-byte load.
-    auto signs_in_tile_order = [&](const std::vector<int32_t>& slot_rows, uint32_t* out) -> int {
-        std::vector<int32_t> order(slot_rows.size());
-        for (size_t s0 = 0; s0 < slot_rows.size(); s0 += kWave)
-            for (int i = 0; i < 16; ++i)
-                for (int t = 0; t < 4; ++t) order[s0 + 4 * i + t] = slot_rows[s0 + 16 * t + i];
-        int32_t* tmp = nullptr;
-        int rc2 = dev_alloc(&tmp, order.size());
-        if (rc2 != APB_OK) return rc2;
-        hipError_t e = hipMemcpyAsync(tmp, order.data(), order.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) rc2 = launch_slot_major_signs(d.sign, tmp, d.rows_Nr, d.Kw, d.rows_Kw4, out, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);        // `order` and `tmp` are released below
-        (void)hipFree(tmp);
-        if (rc2 != APB_OK) return rc2;
-        APB_HIP(e);
-        return APB_OK;
-    };
-    std::vector<uint32_t> rek;
-    std::vector<double> rev, rvalsum;
-    if ((long long)32 * d.Kw * kRowsStageBytesPerK <= kRowsMaxTableBytes && nnz >= (long long)4 * N) {
-        build_row_lists(hrow_ptr, hcol, hval, rperm, rblk, rek, rev, rvalsum, 0);
-        const long long steps = rblk.back();
-        if (steps * kWave <= 2 * nnz) {                   // at most half of the list entries are padding
-            d.rows_Nr = (int)rperm.size();
-            d.rows_Kw4 = 4 * ((d.Kw + 3) / 4);
-            d.rows_steps = steps;
-            if ((rc = dev_alloc(&d.rows_perm, rperm.size())) != APB_OK) return rc;
-            if ((rc = dev_alloc(&d.rows_blk, rblk.size())) != APB_OK) return rc;
-            if ((rc = dev_alloc(&d.rows_ek, rek.size())) != APB_OK) return rc;
-            if ((rc = dev_alloc(&d.rows_ev, rev.size())) != APB_OK) return rc;
-            if ((rc = dev_alloc(&d.rows_valsum, rvalsum.size())) != APB_OK) return rc;
-            if ((rc = dev_alloc(&d.rows_sign, (size_t)d.rows_Kw4 * d.rows_Nr)) != APB_OK) return rc;
-            APB_HIP(hipMemcpyAsync(d.rows_perm, rperm.data(), rperm.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-            APB_HIP(hipMemcpyAsync(d.rows_blk, rblk.data(), rblk.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-            APB_HIP(hipMemcpyAsync(d.rows_ek, rek.data(), rek.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-            APB_HIP(hipMemcpyAsync(d.rows_ev, rev.data(), rev.size() * sizeof(double), hipMemcpyHostToDevice, s));
-            APB_HIP(hipMemcpyAsync(d.rows_valsum, rvalsum.data(), rvalsum.size() * sizeof(double), hipMemcpyHostToDevice, s));
-            if ((rc = signs_in_tile_order(rperm, d.rows_sign)) != APB_OK) return rc;
-            // the word-aligned lists beside them (more than one group of rows; the same padding rule)
-            if (N > kRowsGroupRows) {
-                APB_HIP(hipStreamSynchronize(s));              // the staging vectors above are reused
-                build_row_lists(hrow_ptr, hcol, hval, rperm, rblk, rek, rev, rvalsum, kRowsGroupRows);
-                const long long wsteps = rblk.back();
-                if (wsteps * kWave <= 2 * nnz) {
-                    d.rowsw_steps = wsteps;
-                    if ((rc = dev_alloc(&d.rowsw_perm, rperm.size())) != APB_OK) return rc;
-                    if ((rc = dev_alloc(&d.rowsw_blk, rblk.size())) != APB_OK) return rc;
-                    if ((rc = dev_alloc(&d.rowsw_ek, rek.size())) != APB_OK) return rc;
-                    if ((rc = dev_alloc(&d.rowsw_ev, rev.size())) != APB_OK) return rc;
-                    if ((rc = dev_alloc(&d.rowsw_valsum, rvalsum.size())) != APB_OK) return rc;
-                    if ((rc = dev_alloc(&d.rowsw_sign, (size_t)d.rows_Kw4 * d.rows_Nr)) != APB_OK) return rc;
-                    APB_HIP(hipMemcpyAsync(d.rowsw_perm, rperm.data(), rperm.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-                    APB_HIP(hipMemcpyAsync(d.rowsw_blk, rblk.data(), rblk.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-                    APB_HIP(hipMemcpyAsync(d.rowsw_ek, rek.data(), rek.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-                    APB_HIP(hipMemcpyAsync(d.rowsw_ev, rev.data(), rev.size() * sizeof(double), hipMemcpyHostToDevice, s));
-                    APB_HIP(hipMemcpyAsync(d.rowsw_valsum, rvalsum.data(), rvalsum.size() * sizeof(double), hipMemcpyHostToDevice, s));
-                    if ((rc = signs_in_tile_order(rperm, d.rowsw_sign)) != APB_OK) return rc;
-                }
+    if (K <= kRowsMaxK) {
+        DigitSteps ds;
+        build_digit_steps(N, hrow_ptr, hcol, hval, K <= kRowsByteK, ds);
+        const int tiles = 2 * ((N + 31) / 32);
+        d.rows_ksteps = (d.Kw + 3) / 4;
+        d.rows_windows = ds.windows;
+        d.rows_unit_log2 = ds.unit;
+        d.rows_steps = ds.first.back();
+        int longest = 0;
+        for (int c : hcounts) longest = std::max(longest, c);
+        d.rows_short = longest <= kShortRow;
+        d.rows_rich = N > 192 && nnz >= (long long)4 * N && (long long)32 * longest <= nnz;
+        std::vector<uint32_t> hsign((size_t)N * d.Kw), sg((size_t)tiles * d.rows_ksteps * 64, 0u);
+        APB_HIP(hipMemcpyAsync(hsign.data(), d.sign, hsign.size() * 4, hipMemcpyDeviceToHost, s));
+        APB_HIP(hipStreamSynchronize(s));
+        for (int n = 0; n < N; ++n)
+            for (int j = 0; j < d.Kw; ++j) {
+                uint32_t w = hsign[(size_t)n * d.Kw + j];
+                const int g = j & 3;
+                if (g & 1) w = ((w & 0x33333333u) << 2) | ((w >> 2) & 0x33333333u);
+                sg[((size_t)(n / 16) * d.rows_ksteps + j / 4) * 64 + 16 * g + n % 16] = w;
             }
-        }
+        if ((rc = dev_alloc(&d.rows_sign, sg.size())) != APB_OK) return rc;
+        if ((rc = dev_alloc(&d.rows_first, ds.first.size())) != APB_OK) return rc;
+        if ((rc = dev_alloc(&d.rows_count, ds.count.size() + 16)) != APB_OK) return rc;
+        if ((rc = dev_alloc(&d.rows_step, ds.step.size())) != APB_OK) return rc;
+        if ((rc = dev_alloc(&d.rows_valsum, ds.valsum.size())) != APB_OK) return rc;
+        APB_HIP(hipMemcpyAsync(d.rows_sign, sg.data(), sg.size() * 4, hipMemcpyHostToDevice, s));
+        APB_HIP(hipMemcpyAsync(d.rows_first, ds.first.data(), ds.first.size() * 4, hipMemcpyHostToDevice, s));
+        APB_HIP(hipMemcpyAsync(d.rows_count, ds.count.data(), ds.count.size(), hipMemcpyHostToDevice, s));
+        APB_HIP(hipMemcpyAsync(d.rows_step, ds.step.data(), ds.step.size(), hipMemcpyHostToDevice, s));
+        APB_HIP(hipMemcpyAsync(d.rows_valsum, ds.valsum.data(), ds.valsum.size() * 8, hipMemcpyHostToDevice, s));
+        APB_HIP(hipStreamSynchronize(s));
     }
     APB_HIP(hipStreamSynchronize(s));                 // host staging vectors go out of scope after this
     return APB_OK;
@@ -452,18 +487,21 @@ int apb_forward_requant(const apb_layer* layer, const void* packed, int M, int b
     const int32_t* colsum = reinterpret_cast<const int32_t*>(planes + (size_t)bits * d.Kw * Mp);
     hipStream_t s = as_stream(stream);
     uint32_t* out = static_cast<uint32_t*>(packed_out);
+    if (forward_rows_applies(d, bits))
+        return launch_forward_rows_requant(d, planes, colsum, M, bits, step, nullptr, nullptr, scale, shift, bits_out,
+                                           1.0f / step_out, out, s);
     return launch_forward_requant(d, planes, colsum, M, bits, step, nullptr, scale, shift, bits_out, 1.0f / step_out, out, s);
 }
 
 const char* apb_forward_kernel_name(const apb_layer* layer, int M, int bits) {
     if (!layer || M <= 0 || (bits != 1 && bits != 2)) return "";
-    if (forward_rows_applies(layer->d, M, bits)) return forward_rows_kernel_name(layer->d, M, bits);
+    if (forward_rows_applies(layer->d, bits)) return forward_rows_kernel_name(layer->d, M, bits);
     return forward_kernel_name(layer->d, M, bits);
 }
 
 int apb_quantize_forward_is_one_kernel(const apb_layer* layer, int M, int bits) {
     if (!layer || M <= 0 || (bits != 1 && bits != 2)) return 0;
-    return forward_float_applies(layer->d, M, bits) ? 1 : 0;
+    return forward_rows_float_applies(layer->d, M, bits) ? 1 : 0;
 }
 
 int apb_quantize_forward(const apb_layer* layer, const float* X, int M, int bits, float step, void* packed, float* Y,
@@ -474,7 +512,7 @@ int apb_quantize_forward(const apb_layer* layer, const float* X, int M, int bits
     if (bits != 1 && bits != 2) return APB_ERR_BITS;
     if (!std::isfinite(step) || !(step > 0.0f)) return APB_ERR_VALUE;
     hipStream_t s = as_stream(stream);
-    if (forward_float_applies(d, M, bits)) return launch_forward_float(d, X, M, bits, step, Y, s);
+    if (forward_rows_float_applies(d, M, bits)) return launch_forward_rows_float(d, X, M, bits, step, Y, s);
     uint32_t* planes = static_cast<uint32_t*>(packed);
     int32_t* colsum = reinterpret_cast<int32_t*>(planes + (size_t)bits * d.Kw * ((size_t)kWave * (((size_t)M + kWave - 1) / kWave)));
     return launch_quantize_then_forward(d, X, M, bits, step, planes, colsum, Y, s);
@@ -498,23 +536,12 @@ static int conv_shape(const LayerDev& d, int B, int H, int W, int stride, ConvSh
     return APB_OK;
 }
 
-// With a workspace, layers on which the rows-in-lanes kernel applies write the packed patch matrix there first and
-// run the plain-matrix kernels on it; `patches` is null otherwise.
-static int conv_patches(const LayerDev& d, const uint32_t* planes, const int32_t* pixsum, int P, int bits,
-                        const ConvShape& conv, void* workspace, size_t workspace_bytes, uint32_t* clear, size_t clear_words,
-                        hipStream_t s, const uint32_t** patches, const int32_t** colsum) {
-    *patches = nullptr;
-    *colsum = nullptr;
+// The caller's workspace where it takes the packed patch matrix (null: it does not, or the layer leaves none).
+static uint32_t* patch_matrix(const LayerDev& d, int P, int bits, void* workspace, size_t workspace_bytes) {
     const size_t Pp = (size_t)kWave * (((size_t)P + kWave - 1) / kWave);
     const size_t need = sizeof(uint32_t) * Pp * ((size_t)bits * d.Kw + 1);
-    if (!workspace || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return APB_OK;
-    if (!forward_rows_applies(d, P, bits)) return APB_OK;
-    uint32_t* out = static_cast<uint32_t*>(workspace);
-    const int rc = launch_pack_patches(d, planes, pixsum, P, bits, conv, out, clear, clear_words, s);
-    if (rc != APB_OK) return rc;
-    *patches = out;
-    *colsum = reinterpret_cast<const int32_t*>(out + (size_t)bits * d.Kw * Pp);
-    return APB_OK;
+    if (!workspace || workspace_bytes < need || !d.rows_rich) return nullptr;
+    return static_cast<uint32_t*>(workspace);
 }
 
 int apb_forward_conv3x3(const apb_layer* layer, const void* fmap, int B, int H, int W, int stride, int bits, float step,
@@ -530,11 +557,8 @@ int apb_forward_conv3x3(const apb_layer* layer, const void* fmap, int B, int H, 
     hipStream_t s = as_stream(stream);
     const uint32_t* planes = static_cast<const uint32_t*>(fmap);
     const int32_t* pixsum = reinterpret_cast<const int32_t*>(planes + (size_t)bits * (conv.C / 32) * conv.Pp_in);
-    const uint32_t* patches;
-    const int32_t* colsum;
-    if ((rc = conv_patches(d, planes, pixsum, P, bits, conv, workspace, workspace_bytes, nullptr, 0, s, &patches, &colsum)) != APB_OK)
-        return rc;
-    if (patches) return launch_forward_best(d, patches, colsum, P, bits, step, Y, s);
+    if (forward_rows_applies(d, bits))
+        return launch_forward_rows(d, planes, nullptr, P, bits, step, &conv, patch_matrix(d, P, bits, workspace, workspace_bytes), Y, s);
     return launch_forward(d, planes, pixsum, P, bits, step, &conv, Y, s);
 }
 
@@ -553,16 +577,10 @@ int apb_forward_conv3x3_requant(const apb_layer* layer, const void* fmap, int B,
     const int32_t* pixsum = reinterpret_cast<const int32_t*>(planes + (size_t)bits * (conv.C / 32) * conv.Pp_in);
     hipStream_t s = as_stream(stream);
     uint32_t* out = static_cast<uint32_t*>(fmap_out);
-    const uint32_t* patches;
-    const int32_t* colsum;
-    // (the kernel that follows the packed patch matrix ORs its bits into the output: cleared by the same launch)
-    const size_t Pp = (size_t)kWave * (((size_t)P + kWave - 1) / kWave);
-    const size_t out_words = ((size_t)bits_out * ((d.N + 31) / 32) + 1) * Pp;
-    if ((rc = conv_patches(d, planes, pixsum, P, bits, conv, workspace, workspace_bytes, out, out_words, s, &patches, &colsum)) != APB_OK)
-        return rc;
-    if (patches)
-        return launch_forward_requant(d, patches, colsum, P, bits, step, nullptr, scale, shift, bits_out, 1.0f / step_out, out, s,
-                                      true);
+    if (forward_rows_applies(d, bits))
+        return launch_forward_rows_requant(d, planes, nullptr, P, bits, step, &conv,
+                                           patch_matrix(d, P, bits, workspace, workspace_bytes), scale, shift, bits_out,
+                                           1.0f / step_out, out, s);
     return launch_forward_requant(d, planes, pixsum, P, bits, step, &conv, scale, shift, bits_out, 1.0f / step_out, out, s);
 }
 

@@ -43,38 +43,45 @@ struct LayerDev {
     int32_t* seg_ptr = nullptr;    // [Np/kRowTile][nchunks+1]  first block of (tile, chunk)
     uint32_t* ent = nullptr;       // [blocks][24]  8 keys: 2 * row_in_tile | (col - 256*chunk) << 8, then
                                    //               8 float64: residual * 2^kEntValScaleLog2 (0 for padding)
-    // Row lists for the rows-in-lanes forward kernel (apb_rows.hip), built for layers with many residuals
-    // per row whose K fits the on-chip code table; rows_steps == 0 when not built.  Rows are sorted by
-    // residual count and cut into blocks of 64 launch slots; block b walks steps rows_blk[b] .. rows_blk[b+1],
-    // and in a step lane l handles one residual of its row (or a padding entry: offset 0, value 0).
-    int rows_Nr = 0;               // 64 * blocks
-    int rows_Kw4 = 0;              // Kw rounded up to a multiple of 4 (one matrix step = 128 values of k)
+    // What the matrix-core forward kernel (apb_rows.hip) reads; rows_steps == 0 when not built (K beyond its table).
+    // Rows go in tiles of 16; a tile is two quads of four pairs of rows, in this order: for r = 0, 1 (first quad), 2, 3
+    // (second) the rows (r, 8 + r), then (4 + r, 12 + r).
+    int rows_ksteps = 0;           // K in steps of 128, rounded up
+    int rows_unit_log2 = 0;        // the residuals are whole multiples of 2^rows_unit_log2 ...
+    int rows_windows = 1;          // ... and are cut into this many windows of kWindowBits bits
+    bool rows_short = true;        // no row has more than kShortRow residuals
+    bool rows_rich = false;        // 192 rows and more that carry 4 residuals or more, in lists of similar lengths
     long long rows_steps = 0;
-    int32_t* rows_perm = nullptr;  // [Nr]        row served by slot i, -1 for padding
-    int32_t* rows_blk = nullptr;   // [Nr/64 + 1]
-    uint32_t* rows_ek = nullptr;   // [steps][64] kRowsRowBytes * column: byte offset of the column's row in the code table
-    double* rows_ev = nullptr;     // [steps][64] residual * 2^kEntValScaleLog2
-    uint32_t* rows_sign = nullptr; // [Kw4][Nr]   sign words of the slots (pad rows and slots zero); inside a block of 64
-                                   //             slots, slot 16 * t + i sits at position 4 * i + t (the order the matrix tiles take them)
-    double* rows_valsum = nullptr; // [Nr]        sum of the residuals of the slot's row (float64, CSR order)
-    // The same lists with the rows sorted by residual count only inside groups of kRowsGroupRows consecutive rows
-    // (whole 32-row words of a packed output): a workgroup of the packed-output epilogue that takes one such group
-    // owns its output words -- plain stores, nothing to clear, no atomics.  Built for layers of more than one
-    // group (otherwise the lists above already are of this kind); rowsw_steps == 0 when not built.
-    long long rowsw_steps = 0;
-    int32_t* rowsw_perm = nullptr;
-    int32_t* rowsw_blk = nullptr;
-    uint32_t* rowsw_ek = nullptr;
-    double* rowsw_ev = nullptr;
-    uint32_t* rowsw_sign = nullptr;
-    double* rowsw_valsum = nullptr;
+    uint32_t* rows_sign = nullptr; // [tiles][ksteps][64]     sign words in the order the binary part's lanes take them:
+                                   //           lane (i, g): word 4 * step + g of row 16 * tile + i, the bit pairs of every
+                                   //           nibble swapped for odd g; zero outside the matrix
+    int32_t* rows_first = nullptr; // [tiles]                 first digit step of a tile
+    uint8_t* rows_count = nullptr; // [tiles][2 quads][windows]  digit steps of each pair of a quad (see digit_steps_of)
+    uint8_t* rows_step = nullptr;  // [steps][kStepBytes]     see kStepBytes
+    double* rows_valsum = nullptr; // [16 * tiles]            sum of the residuals of the row (float64, CSR order)
 };
 
-constexpr int kRowsCols = 16;            // output columns one workgroup of the rows-in-lanes kernel covers
-constexpr int kRowsGroupRows = 256;      // rows of one group of the word-aligned lists: 4 blocks of 64, 8 output words
-constexpr int kRowsRowBytes = 8;         // bytes of its code table per value of k (two dwords of 8 columns x 2 bits)
-constexpr int kRowsStageBytesPerK = 8;   // LDS per value of k of its staged activation operand (16 columns x FP4)
-constexpr int kRowsMaxTableBytes = 144 * 1024;   // the staged operand of all of K, and the table after it, have to fit on chip
+// A digit step of the matrix-core forward kernel: up to 128 values of k at which one of the two rows of a pair has a
+// residual.  Lane block g (of 4) holds values 32 * g .. 32 * g + 31 of the step:
+//   16 + 8 bytes for each of 48 lanes (12 digit rows x 4 blocks: row 6 * half + digit, block g at 12 * g + row): 32 FP6
+//   numbers, the digits of the residuals at these k (0 where the row has none); first all the 16s, then all the 8s;
+//   one word for each of 64 lanes (i, g): row of value 32 * g + i | row of value 32 * g + 16 + i << 16, where row is the
+//   byte offset 8 * k in the code table (layers of K <= kRowsByteK) or k.
+// A digit d is the FP6 (E2M3) number d / 8 at an even k and d / 4 at an odd one.  kStepPad more steps follow the last one.
+constexpr int kStepA8 = 48 * 16;
+constexpr int kStepRows = 48 * 24;
+constexpr int kStepBytes = 48 * 24 + 64 * 4;
+// Steps each pair of a quad takes when its longest list has `entries`: what the kernel has straight code for (1, 2, 3,
+// 4 and 6), or whole rounds of its four registers sets.
+__host__ __device__ inline int digit_steps_of(int entries) {
+    const int s = (entries + 127) / 128;
+    return s <= 1 ? 1 : s <= 4 ? s : s <= 6 ? 6 : (s + 3) / 4 * 4;
+}
+constexpr int kStepPad = 8;
+constexpr int kRowsByteK = 8192;
+constexpr int kWindowBits = 30;              // six base-32 digits, -16 .. 16
+constexpr int kShortRow = 330;               // residuals of a row whose three-digit sums stay below 2^24: 330 * 3 * 16 * (1 + 32 + 1024)
+constexpr int kRowsMaxK = 18432;             // the code table of one column group (8 bytes per value of k): 144 KB of LDS
 
 void set_last_hip_error(hipError_t e);
 
@@ -144,38 +151,32 @@ struct ConvShape {
 };
 int launch_forward(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
                    const ConvShape* conv, float* Y, hipStream_t s);
-// the packed patch matrix of a convolution (9 * C x M, as apb_quantize_acts lays a matrix out) written into `out`
-// (and, on the side, `clear_words` words at `clear` set to zero)
-int launch_pack_patches(const LayerDev& L, const uint32_t* planes, const int32_t* pixsum, int M, int bits,
-                        const ConvShape& conv, uint32_t* out, uint32_t* clear, size_t clear_words, hipStream_t s);
 const char* forward_kernel_name(const LayerDev& L, int M, int bits);
-// quantize + forward in one kernel, from the float matrix X (K x M): same Y, bit for bit, as launch_quantize +
-// launch_forward; only where forward_float_applies says so (APB_ERR_SHAPE otherwise)
-bool forward_float_applies(const LayerDev& L, int M, int bits);
-int launch_forward_float(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s);
 // the same with the next layer's quantizer applied to scale[n] * Y + shift[n] (scale, shift nullable) and
 // the codes packed into `packed_out` (K = L.N, same M), fully overwritten
 int launch_forward_requant(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
                            const ConvShape* conv, const float* scale, const float* shift, int bits_out,
-                           float inv_step_out, uint32_t* packed_out, hipStream_t s, bool out_cleared = false);
-// (out_cleared: packed_out is known to be all zero already -- only the kernels that OR into it care)
+                           float inv_step_out, uint32_t* packed_out, hipStream_t s);
 
 // true while K * max_weight * max_code < 2^24: the float accumulators of the matrix instruction then hold
 // every partial sum exactly (launchers return APB_ERR_SHAPE otherwise)
 bool mfma_sum_exact(int K, int max_weight, int max_code);
 
-// the rows-in-lanes forward kernel (apb_rows.hip): same Y as launch_forward for a plain K x M matrix;
-// forward_rows_applies says whether the layer has row lists and the launch is worth it
-bool forward_rows_applies(const LayerDev& L, int M, int bits);
+// the matrix-core forward kernel (apb_rows.hip): same Y as launch_forward.  colsum == nullptr: the kernel adds the
+// code sums of its columns up from the packed words (always so for convolutions).  patches (convolutions; may be
+// null): the packed patch matrix, 9 * C x M as apb_quantize_acts lays a matrix out, is left there as well.
+bool forward_rows_applies(const LayerDev& L, int bits);
 const char* forward_rows_kernel_name(const LayerDev& L, int M, int bits);
-// colsum == nullptr: the kernel adds the code sums of its columns up from the packed words
 int launch_forward_rows(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
-                        float* Y, hipStream_t s);
-// the rows-in-lanes kernel ending in the next layer's quantizer (what launch_forward_requant does on a plain matrix)
-bool forward_rows_requant_applies(const LayerDev& L, const uint32_t* planes, int M, int bits);
-int launch_forward_rows_requant(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits,
-                                float step, const float* scale, const float* shift, int bits_out, float inv_step_out,
-                                uint32_t* packed_out, hipStream_t s, bool out_cleared = false);
+                        const ConvShape* conv, uint32_t* patches, float* Y, hipStream_t s);
+// from the float matrix X (K x M), quantize + forward in one kernel: same Y, bit for bit, as launch_quantize +
+// launch_forward_rows; only where forward_rows_float_applies says so (APB_ERR_SHAPE otherwise)
+bool forward_rows_float_applies(const LayerDev& L, int M, int bits);
+int launch_forward_rows_float(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s);
+// ending in the next layer's quantizer (see launch_forward_requant)
+int launch_forward_rows_requant(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
+                                const ConvShape* conv, uint32_t* patches, const float* scale, const float* shift,
+                                int bits_out, float inv_step_out, uint32_t* packed_out, hipStream_t s);
 // launch_quantize + launch_forward_best through the scratch buffer planes / colsum (the step of layers that do
 // not run as one kernel); what `colsum` holds afterwards is unspecified
 int launch_quantize_then_forward(const LayerDev& L, const float* X, int M, int bits, float step, uint32_t* planes,
