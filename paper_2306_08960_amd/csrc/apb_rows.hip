@@ -43,6 +43,7 @@
 
 #include "apb_fp4_expand.h"
 #include "apb_internal.h"
+#include "apb_rows_shape.h"
 
 namespace apb {
 
@@ -683,13 +684,6 @@ __global__ APB_ROWS_ATTR void k_forward_light_rows(const RowsArgs a, const RowsP
     rows_task<BITS, SRC, REQ, NT, NCW, GENERAL>(a, p);
 }
 
-constexpr int kComputeUnits = 256;                             // of the MI355X
-constexpr int kMaxLdsBytes = 160 * 1024;
-
-int rows_lds_bytes(int ksteps, int groups, int meta_tiles, bool req, int bits) {
-    return groups * (ksteps * 1024 + 128) + 1024 + 16 * meta_tiles * ((req ? 8 : 0) + (bits == 1 ? 12 : 0));
-}
-
 // The kernels address their LDS from address 0: true while they have no static LDS in front of the dynamic array.
 // Checked once per kernel and process, from the kernel's own attributes; a launch of more LDS than a kernel gets
 // without asking is asked for once per device and kernel.
@@ -720,79 +714,7 @@ int launch_kernel(const RowsArgs& a, const RowsParams& p, long long wgs, int wav
     return APB_OK;
 }
 
-struct Shape {
-    int groups, nt, ncw, waves, chunk;
-};
-
-constexpr int kFloatRows = 128;
-
 bool is_general(const LayerDev& L) { return L.rows_windows > 1 || !L.rows_short || L.K > kRowsByteK; }
-
-// How many tiles a workgroup takes (of all, shared evenly) and how many waves work on them.  The time of a launch,
-// in units of a fifth of an item (an item alone on its SIMD takes five): rounds of workgroups on the chip, times the
-// items a wave takes one after another (two waves on a SIMD take 1.5 times as long, four 2.5 times: the matrix cores,
-// the LDS and the L1 fill are shared, latencies overlap) and the table build (which more waves finish sooner).
-void spread(const LayerDev& L, Shape& h, long long cts, int max_waves, int waves_per_cu) {
-    const int tiles = 2 * ((L.N + 31) / 32), shares = h.groups / h.ncw;
-    const int lds = h.groups * (L.rows_ksteps * 1024 + 1024);
-    double best = 1e300;
-    int chunk = (tiles + h.nt - 1) / h.nt * h.nt;
-    for (;;) {
-        const int items = chunk / h.nt * shares, parts = (tiles + chunk - 1) / chunk;
-        int waves = shares;
-        while (waves < max_waves && waves < items) waves *= 2;
-        const long long wgs = cts * parts;
-        const int fit = std::max(1, std::min(kMaxLdsBytes / lds, waves_per_cu / waves));
-        const long long per_cu = std::min<long long>(fit, (wgs + kComputeUnits - 1) / kComputeUnits);
-        const double rounds = wgs <= (long long)kComputeUnits * per_cu ? 1.0 : (double)wgs / (kComputeUnits * per_cu);
-        const int active = std::min(waves, items);
-        const double crowd = 0.5 + 0.5 * (double)((per_cu * active + 3) / 4);
-        const double cost = (rounds > 1.0 && rounds < 4.0 ? std::ceil(rounds) : rounds) * (5.0 * ((items + waves - 1) / waves) * crowd + 16.0 / waves);
-        if (cost < best * 0.97) {                                // (fewer workgroups where it makes no difference)
-            best = cost;
-            h.chunk = chunk;
-            h.waves = waves;
-        }
-        if (chunk <= h.nt) break;
-        chunk = (chunk / 2 + h.nt - 1) / h.nt * h.nt;
-    }
-}
-
-Shape pick_shape(const LayerDev& L, int M, Source kind, int bits) {
-    Shape h;
-    const int tiles = 2 * ((L.N + 31) / 32), ksteps = L.rows_ksteps;
-    const long long ct16 = (M + 15) / 16, ct64 = (M + 63) / 64;
-    if (is_general(L)) {
-        h.groups = ksteps <= 72 ? 2 : 1;
-        h.nt = h.ncw = 1;
-        spread(L, h, (M + 16 * h.groups - 1) / (16 * h.groups), 8, 16);
-        return h;
-    }
-    if (kind == kFloat && L.N <= kFloatRows && ct16 >= 4 * kComputeUnits) {
-        // Rows of X are read 64 or 32 columns (two or one lines of memory) at a time, by a workgroup that has all rows of the layer.
-        h = Shape{tiles <= 4 ? 4 : 2, 2, 2, 4, tiles};
-        return h;
-    }
-    if ((ct16 + 1) / 2 * (tiles / 2) < 4 * kComputeUnits && (ksteps <= 19 || ct64 * tiles < 2 * kComputeUnits || ksteps > 38)) {
-        // Few items: single tiles of one column group, in as many workgroups as give every SIMD of the chip a wave.
-        h = Shape{1, 1, 1, 2, 2};
-        while (ct16 * ((tiles + h.chunk - 1) / h.chunk) > 4 * kComputeUnits) h.chunk *= 2;
-        h.waves = std::min(8, h.chunk);
-        return h;
-    }
-    if (ksteps > 19 && ksteps <= 38) {
-        // Long K, one workgroup per CU whatever the shape: 64 columns per item, so that a digit step fetched through the
-        // L1 (64 bytes a clock: 22 clocks) serves four matrix instructions.
-        h = Shape{4, 1, 4, 8, tiles};
-        spread(L, h, ct64, 8, 8);
-        h.waves = 8;                                             // (at least two waves per SIMD to build 150 KB of tables)
-        return h;
-    }
-    h.groups = ksteps <= 19 && tiles <= 4 ? 4 : 2;
-    h.nt = h.ncw = 2;
-    spread(L, h, (M + 16 * h.groups - 1) / (16 * h.groups), 8, 16);
-    return h;
-}
 
 template <int BITS, int SRC, bool REQ, int NT, int NCW, bool GENERAL>
 int launch_named(const LayerDev& L, const RowsArgs& a, const RowsParams& p, long long wgs, int waves, int lds, hipStream_t s) {
@@ -801,8 +723,7 @@ int launch_named(const LayerDev& L, const RowsArgs& a, const RowsParams& p, long
 }
 
 template <int BITS, int SRC, bool REQ>
-int launch_shape(const LayerDev& L, const RowsArgs& a, const RowsParams& p, const Shape& h, long long wgs, hipStream_t s) {
-    const int lds = rows_lds_bytes(p.ksteps, p.groups, p.chunk, REQ, BITS);
+int launch_shape(const LayerDev& L, const RowsArgs& a, const RowsParams& p, const RowsShape& h, long long wgs, int lds, hipStream_t s) {
     if (is_general(L)) return launch_named<BITS, SRC, REQ, 1, 1, true>(L, a, p, wgs, h.waves, lds, s);
     switch (8 * h.nt + h.ncw) {
         case 9: return launch_named<BITS, SRC, REQ, 1, 1, false>(L, a, p, wgs, h.waves, lds, s);
@@ -834,7 +755,8 @@ int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* c
     const long long Mp = (long long)kWave * (((long long)M + kWave - 1) / kWave);
     if (Mp * 8 >= (1LL << 31)) return APB_ERR_SHAPE;
     const bool req = o.bits != 0;
-    const Shape h = pick_shape(L, M, kind, bits);
+    const RowsProblem q{L.N, M, L.rows_ksteps, bits, is_general(L), req, kind == kFloat};
+    const RowsShape h = pick_rows_shape(q);
     RowsParams p{};
     p.alpha = (double)L.alpha * (double)step;
     p.step = (double)step;
@@ -845,7 +767,7 @@ int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* c
     p.Mp = (int)Mp;
     p.M = M;
     p.ksteps = L.rows_ksteps;
-    p.tiles = 2 * ((L.N + 31) / 32);
+    p.tiles = rows_tiles(L.N);
     p.windows = L.rows_windows;
     p.groups = h.groups;
     p.groups_log2 = log2_of(h.groups);
@@ -854,7 +776,8 @@ int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* c
     p.chunk = std::min(h.chunk, p.tiles);
     p.parts = (p.tiles + p.chunk - 1) / p.chunk;
     const long long wgs = (cols + 16 * h.groups - 1) / (16 * h.groups) * p.parts;
-    if (wgs > 0x7fffffffLL) return APB_ERR_SHAPE;
+    const long long lds = rows_lds_bytes(q, h.groups, p.chunk);
+    if (wgs <= 0 || wgs > 0x7fffffffLL || lds > kMaxLdsBytes) return APB_ERR_SHAPE;
     p.row_shift = L.K > kRowsByteK ? 3 : 0;
     p.out_bits = o.bits;
     p.out_Kw = (L.N + 31) / 32;
@@ -879,14 +802,14 @@ int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* c
                      o.scale, o.shift, patches, o.out};
     if (kind == kFloat) {
         if (req) return APB_ERR_SHAPE;
-        return bits == 1 ? launch_shape<1, kFloat, false>(L, a, p, h, wgs, s) : launch_shape<2, kFloat, false>(L, a, p, h, wgs, s);
+        return bits == 1 ? launch_shape<1, kFloat, false>(L, a, p, h, wgs, (int)lds, s) : launch_shape<2, kFloat, false>(L, a, p, h, wgs, (int)lds, s);
     }
     if (kind == kConv) {
-        if (req) return bits == 1 ? launch_shape<1, kConv, true>(L, a, p, h, wgs, s) : launch_shape<2, kConv, true>(L, a, p, h, wgs, s);
-        return bits == 1 ? launch_shape<1, kConv, false>(L, a, p, h, wgs, s) : launch_shape<2, kConv, false>(L, a, p, h, wgs, s);
+        if (req) return bits == 1 ? launch_shape<1, kConv, true>(L, a, p, h, wgs, (int)lds, s) : launch_shape<2, kConv, true>(L, a, p, h, wgs, (int)lds, s);
+        return bits == 1 ? launch_shape<1, kConv, false>(L, a, p, h, wgs, (int)lds, s) : launch_shape<2, kConv, false>(L, a, p, h, wgs, (int)lds, s);
     }
-    if (req) return bits == 1 ? launch_shape<1, kPlanes, true>(L, a, p, h, wgs, s) : launch_shape<2, kPlanes, true>(L, a, p, h, wgs, s);
-    return bits == 1 ? launch_shape<1, kPlanes, false>(L, a, p, h, wgs, s) : launch_shape<2, kPlanes, false>(L, a, p, h, wgs, s);
+    if (req) return bits == 1 ? launch_shape<1, kPlanes, true>(L, a, p, h, wgs, (int)lds, s) : launch_shape<2, kPlanes, true>(L, a, p, h, wgs, (int)lds, s);
+    return bits == 1 ? launch_shape<1, kPlanes, false>(L, a, p, h, wgs, (int)lds, s) : launch_shape<2, kPlanes, false>(L, a, p, h, wgs, (int)lds, s);
 }
 
 }  // namespace
@@ -895,18 +818,12 @@ bool forward_rows_applies(const LayerDev& L, int bits) {
     return L.rows_steps > 0 && mfma_sum_exact(L.K, 1, bits == 1 ? 1 : 3);
 }
 
-// Quantize + forward in one kernel: where one workgroup holds every row of the layer, so that no column of X is
-// quantized twice, and the columns fill the chip (a narrow tail of them would read X with too few waves); and where X is
-// so small (a quarter of a MB: every workgroup's share comes from the L2) that the launches saved are worth more.
 bool forward_rows_float_applies(const LayerDev& L, int M, int bits) {
-    if (!forward_rows_applies(L, bits)) return false;
-    if ((long long)L.K * M <= 65536) return true;
-    if (L.N > kFloatRows || L.rows_ksteps > 38) return false;
-    return L.N <= kFloatRows / 2 || M >= 64 * 375;
+    return forward_rows_applies(L, bits) && rows_from_float(L.N, L.K, M);
 }
 
 const char* forward_rows_kernel_name(const LayerDev& L, int M, int bits) {
-    const Shape h = pick_shape(L, M, kPlanes, bits);
+    const RowsShape h = pick_rows_shape({L.N, M, L.rows_ksteps, bits, is_general(L), false, false});
 #define APB_NAMES(K, B) \
     {#K "<" #B ", 0, false, 1, 1, true>", #K "<" #B ", 0, false, 1, 1, false>", #K "<" #B ", 0, false, 1, 2, false>", \
      #K "<" #B ", 0, false, 1, 4, false>", #K "<" #B ", 0, false, 2, 2, false>"}
