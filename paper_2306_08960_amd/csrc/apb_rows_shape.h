@@ -50,13 +50,15 @@ inline long long rows_lds_bytes(const RowsProblem& q, int groups, int chunk) {
 // How many tiles a workgroup takes (of all, shared evenly) and how many waves work on them.  The time of a launch,
 // in units of a fifth of an item (an item alone on its SIMD takes five): rounds of workgroups on the chip, times the
 // items a wave takes one after another (two waves on a SIMD take 1.5 times as long, four 2.5 times: the matrix cores,
-// the LDS and the L1 fill are shared, latencies overlap) and the table build (which more waves finish sooner).
+// the LDS and the L1 fill are shared, latencies overlap) and the table build (which more waves finish sooner).  Next
+// to large tables the rows' own sums may leave room for a share of the tiles only.
 inline void rows_spread(const RowsProblem& q, RowsShape& h, long long cts, int max_waves, int waves_per_cu) {
     const int tiles = rows_tiles(q.N), shares = h.groups / h.ncw;
-    const int lds = h.groups * (q.ksteps * 1024 + 1024);
     double best = 1e300;
     int chunk = (tiles + h.nt - 1) / h.nt * h.nt;
+    while (chunk > h.nt && rows_lds_bytes(q, h.groups, chunk) > kMaxLdsBytes) chunk = (chunk / 2 + h.nt - 1) / h.nt * h.nt;
     for (;;) {
+        const int lds = (int)rows_lds_bytes(q, h.groups, chunk) + 896 * h.groups;   // (in kilobytes per column group)
         const long long items = (long long)chunk / h.nt * shares, parts = ((long long)tiles + chunk - 1) / chunk;
         int waves = shares;
         while (waves < max_waves && waves < items) waves *= 2;

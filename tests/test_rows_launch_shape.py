@@ -72,3 +72,7 @@ def walk(tmp_path, lds_limit):
 
 def test_every_accepted_size_has_a_grid_that_covers_it(tmp_path):
     walk(tmp_path, "(1LL << 40)")
+
+
+def test_no_accepted_size_asks_for_more_lds_than_a_workgroup_has(tmp_path):
+    walk(tmp_path, 160 * 1024)
