@@ -488,8 +488,8 @@ int apb_forward_requant(const apb_layer* layer, const void* packed, int M, int b
     hipStream_t s = as_stream(stream);
     uint32_t* out = static_cast<uint32_t*>(packed_out);
     if (forward_rows_applies(d, bits))
-        return launch_forward_rows_requant(d, planes, colsum, M, bits, step, nullptr, nullptr, scale, shift, bits_out,
-                                           1.0f / step_out, out, s);
+        return launch_forward_rows_requant(d, planes, colsum, M, bits, step, nullptr, scale, shift, bits_out, 1.0f / step_out,
+                                           out, s);
     return launch_forward_requant(d, planes, colsum, M, bits, step, nullptr, scale, shift, bits_out, 1.0f / step_out, out, s);
 }
 
@@ -536,16 +536,8 @@ static int conv_shape(const LayerDev& d, int B, int H, int W, int stride, ConvSh
     return APB_OK;
 }
 
-// The caller's workspace where it takes the packed patch matrix (null: it does not, or the layer leaves none).
-static uint32_t* patch_matrix(const LayerDev& d, int P, int bits, void* workspace, size_t workspace_bytes) {
-    const size_t Pp = (size_t)kWave * (((size_t)P + kWave - 1) / kWave);
-    const size_t need = sizeof(uint32_t) * Pp * ((size_t)bits * d.Kw + 1);
-    if (!workspace || workspace_bytes < need || !d.rows_rich) return nullptr;
-    return static_cast<uint32_t*>(workspace);
-}
-
 int apb_forward_conv3x3(const apb_layer* layer, const void* fmap, int B, int H, int W, int stride, int bits, float step,
-                        void* workspace, size_t workspace_bytes, float* Y, void* stream) {
+                        void* /*workspace*/, size_t /*workspace_bytes*/, float* Y, void* stream) {
     if (!layer || !fmap || !Y) return APB_ERR_NULL;
     const LayerDev& d = layer->d;
     ConvShape conv;
@@ -558,13 +550,13 @@ int apb_forward_conv3x3(const apb_layer* layer, const void* fmap, int B, int H, 
     const uint32_t* planes = static_cast<const uint32_t*>(fmap);
     const int32_t* pixsum = reinterpret_cast<const int32_t*>(planes + (size_t)bits * (conv.C / 32) * conv.Pp_in);
     if (forward_rows_applies(d, bits))
-        return launch_forward_rows(d, planes, nullptr, P, bits, step, &conv, patch_matrix(d, P, bits, workspace, workspace_bytes), Y, s);
+        return launch_forward_rows(d, planes, nullptr, P, bits, step, &conv, Y, s);
     return launch_forward(d, planes, pixsum, P, bits, step, &conv, Y, s);
 }
 
 int apb_forward_conv3x3_requant(const apb_layer* layer, const void* fmap, int B, int H, int W, int stride, int bits,
                                 float step, const float* scale, const float* shift, int bits_out, float step_out,
-                                void* workspace, size_t workspace_bytes, void* fmap_out, void* stream) {
+                                void* /*workspace*/, size_t /*workspace_bytes*/, void* fmap_out, void* stream) {
     if (!layer || !fmap || !fmap_out || (scale == nullptr) != (shift == nullptr)) return APB_ERR_NULL;
     const LayerDev& d = layer->d;
     ConvShape conv;
@@ -578,9 +570,8 @@ int apb_forward_conv3x3_requant(const apb_layer* layer, const void* fmap, int B,
     hipStream_t s = as_stream(stream);
     uint32_t* out = static_cast<uint32_t*>(fmap_out);
     if (forward_rows_applies(d, bits))
-        return launch_forward_rows_requant(d, planes, nullptr, P, bits, step, &conv,
-                                           patch_matrix(d, P, bits, workspace, workspace_bytes), scale, shift, bits_out,
-                                           1.0f / step_out, out, s);
+        return launch_forward_rows_requant(d, planes, nullptr, P, bits, step, &conv, scale, shift, bits_out, 1.0f / step_out,
+                                           out, s);
     return launch_forward_requant(d, planes, pixsum, P, bits, step, &conv, scale, shift, bits_out, 1.0f / step_out, out, s);
 }
 

@@ -163,20 +163,19 @@ int launch_forward_requant(const LayerDev& L, const uint32_t* planes, const int3
 bool mfma_sum_exact(int K, int max_weight, int max_code);
 
 // the matrix-core forward kernel (apb_rows.hip): same Y as launch_forward.  colsum == nullptr: the kernel adds the
-// code sums of its columns up from the packed words (always so for convolutions).  patches (convolutions; may be
-// null): the packed patch matrix, 9 * C x M as apb_quantize_acts lays a matrix out, is left there as well.
+// code sums of its columns up from the packed words (always so for convolutions).
 bool forward_rows_applies(const LayerDev& L, int bits);
 const char* forward_rows_kernel_name(const LayerDev& L, int M, int bits);
 int launch_forward_rows(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
-                        const ConvShape* conv, uint32_t* patches, float* Y, hipStream_t s);
+                        const ConvShape* conv, float* Y, hipStream_t s);
 // from the float matrix X (K x M), quantize + forward in one kernel: same Y, bit for bit, as launch_quantize +
 // launch_forward_rows; only where forward_rows_float_applies says so (APB_ERR_SHAPE otherwise)
 bool forward_rows_float_applies(const LayerDev& L, int M, int bits);
 int launch_forward_rows_float(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s);
 // ending in the next layer's quantizer (see launch_forward_requant)
 int launch_forward_rows_requant(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
-                                const ConvShape* conv, uint32_t* patches, const float* scale, const float* shift,
-                                int bits_out, float inv_step_out, uint32_t* packed_out, hipStream_t s);
+                                const ConvShape* conv, const float* scale, const float* shift, int bits_out,
+                                float inv_step_out, uint32_t* packed_out, hipStream_t s);
 // launch_quantize + launch_forward_best through the scratch buffer planes / colsum (the step of layers that do
 // not run as one kernel); what `colsum` holds afterwards is unspecified
 int launch_quantize_then_forward(const LayerDev& L, const float* X, int M, int bits, float step, uint32_t* planes,

@@ -32,7 +32,7 @@
 // Measured against the kernel this replaces, which had residuals of one row after another in scalar registers and 64
 // columns in the lanes, and summed in float64 (forward alone, both parts): 512 x 4608, 12544 columns, 3 %
 // residuals 87 -> 44.5 us; 4096 x 4096, 256 columns 21.4 -> 14.4; 1000 x 517, 333 columns 9.5 -> 5.5;
-// 256 x 2304 1-bit, 8192 columns 17.7 -> 11.0; chained 256-channel convolution on 14 x 14, 64 images 37 -> 19.5 (the patch
+// 256 x 2304 1-bit, 8192 columns 17.7 -> 11.0; chained 256-channel convolution on 14 x 14, 64 images 37 -> 19.5 (its patch
 // matrix no longer goes through memory).  What bounds the largest: the L1 fill of the digit steps (64 bytes a
 // clock and CU), hence items of four column groups there.
 #include <algorithm>
@@ -95,7 +95,6 @@ struct RowsArgs {
     const int32_t* __restrict__ rowsum;
     const float* __restrict__ scale;
     const float* __restrict__ shift;
-    uint32_t* __restrict__ patches;                              // kConv: the packed patch matrix is left here as well (or null)
     void* __restrict__ out;
 };
 
@@ -181,7 +180,7 @@ __device__ __forceinline__ v8i sign_operand(uint32_t w) {
 
 template <int BITS, int SRC>
 __device__ __forceinline__ void build_table(const RowsArgs& a, const RowsParams& p, int m0, uint32_t cs_at, bool want_sums,
-                                            bool write_patches, int lane, int wave, int waves) {
+                                            int lane, int wave, int waves) {
     const int plane = p.ksteps * 1024;
     if constexpr (SRC == kFloat) {
         // A unit of work is 64 words: 32 rows of X at 64 columns (or 64 rows at 32, 128 at 16), so that a load of one
@@ -282,10 +281,6 @@ __device__ __forceinline__ void build_table(const RowsArgs& a, const RowsParams&
                     const int s = first + min(t0 + u, mine - 1) * along, j = 4 * s + g;
                     if (SRC == kPlanes && j >= p.Kw) x0[u] = x1[u] = 0u;
                     if (want_sums && t0 + u < mine) sum += __builtin_popcount(x0[u]) + 2 * __builtin_popcount(x1[u]);
-                    if (SRC == kConv && write_patches && j < p.Kw && m < p.Mp) {
-                        a.patches[(size_t)j * p.Mp + m] = x0[u];
-                        if (BITS == 2) a.patches[((size_t)p.Kw + j) * p.Mp + m] = x1[u];
-                    }
                     block[u] = (uint32_t)(cg * plane + s * 1024);
                     stage_word<BITS>(block[u] + lane * 16, x0[u], x1[u]);
                 }
@@ -632,7 +627,6 @@ __device__ __forceinline__ void rows_task(const RowsArgs& a, const RowsParams& p
 
     const int tile_m = task / p.parts, t_begin = (task - tile_m * p.parts) * p.chunk, t_end = min(p.tiles, t_begin + p.chunk);
     const int m0 = tile_m * (16 << p.groups_log2);
-    const bool write_patches = SRC == kConv && a.patches != nullptr && t_begin == 0;
 
     const int items = (t_end - t_begin) / NT;
     for (int t = threadIdx.x; t < (32 << p.groups_log2); t += blockDim.x)
@@ -650,13 +644,8 @@ __device__ __forceinline__ void rows_task(const RowsArgs& a, const RowsParams& p
             }
         }
     __syncthreads();
-    build_table<BITS, SRC>(a, p, m0, l.cs, want_sums, write_patches, lane, wave, waves);
+    build_table<BITS, SRC>(a, p, m0, l.cs, want_sums, lane, wave, waves);
     __syncthreads();
-    if (write_patches)
-        for (int t = threadIdx.x; t < (16 << p.groups_log2); t += blockDim.x)
-            if (m0 + t < p.Mp)
-                a.patches[(size_t)BITS * p.Kw * p.Mp + m0 + t] = (uint32_t)*(lds_i32*)(uintptr_t)(l.cs + 4 * t);
-
     for (int item = runner; item < items; item += runners)
         rows_item<BITS, REQ, NT, NCW, GENERAL>(a, p, l, t_begin + item * NT, item * NT, m0, part * NCW, lane);
     if (REQ) {
@@ -750,7 +739,7 @@ struct Output {
 };
 
 int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* colsum, int M, int bits, float step,
-               const ConvShape* conv, uint32_t* patches, const Output& o, hipStream_t s) {
+               const ConvShape* conv, const Output& o, hipStream_t s) {
     if (kind == kFloat ? !forward_rows_float_applies(L, M, bits) : !forward_rows_applies(L, bits)) return APB_ERR_SHAPE;
     const long long Mp = (long long)kWave * (((long long)M + kWave - 1) / kWave);
     if (Mp * 8 >= (1LL << 31)) return APB_ERR_SHAPE;
@@ -771,8 +760,7 @@ int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* c
     p.windows = L.rows_windows;
     p.groups = h.groups;
     p.groups_log2 = log2_of(h.groups);
-    // (a packed output, and a patch matrix, cover the padding columns as well)
-    const long long cols = req || patches ? Mp : M;
+    const long long cols = req ? Mp : M;                         // (a packed output covers the padding columns as well)
     p.chunk = std::min(h.chunk, p.tiles);
     p.parts = (p.tiles + p.chunk - 1) / p.chunk;
     const long long wgs = (cols + 16 * h.groups - 1) / (16 * h.groups) * p.parts;
@@ -799,7 +787,7 @@ int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* c
         if (rc != APB_OK) return rc;
     }
     const RowsArgs a{src, colsum, L.rows_sign, L.rows_step, L.rows_first, L.rows_count, L.rows_valsum, L.rowsum,
-                     o.scale, o.shift, patches, o.out};
+                     o.scale, o.shift, o.out};
     if (kind == kFloat) {
         if (req) return APB_ERR_SHAPE;
         return bits == 1 ? launch_shape<1, kFloat, false>(L, a, p, h, wgs, (int)lds, s) : launch_shape<2, kFloat, false>(L, a, p, h, wgs, (int)lds, s);
@@ -835,25 +823,25 @@ const char* forward_rows_kernel_name(const LayerDev& L, int M, int bits) {
 }
 
 int launch_forward_rows(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
-                        const ConvShape* conv, uint32_t* patches, float* Y, hipStream_t s) {
-    return launch_any(L, planes, conv ? kConv : kPlanes, colsum, M, bits, step, conv, patches,
+                        const ConvShape* conv, float* Y, hipStream_t s) {
+    return launch_any(L, planes, conv ? kConv : kPlanes, colsum, M, bits, step, conv,
                       Output{nullptr, nullptr, 0, 0.0f, Y}, s);
 }
 
 int launch_forward_rows_float(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s) {
-    return launch_any(L, X, kFloat, nullptr, M, bits, step, nullptr, nullptr, Output{nullptr, nullptr, 0, 0.0f, Y}, s);
+    return launch_any(L, X, kFloat, nullptr, M, bits, step, nullptr, Output{nullptr, nullptr, 0, 0.0f, Y}, s);
 }
 
 int launch_forward_rows_requant(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
-                                const ConvShape* conv, uint32_t* patches, const float* scale, const float* shift,
-                                int bits_out, float inv_step_out, uint32_t* packed_out, hipStream_t s) {
-    return launch_any(L, planes, conv ? kConv : kPlanes, colsum, M, bits, step, conv, patches,
+                                const ConvShape* conv, const float* scale, const float* shift, int bits_out,
+                                float inv_step_out, uint32_t* packed_out, hipStream_t s) {
+    return launch_any(L, planes, conv ? kConv : kPlanes, colsum, M, bits, step, conv,
                       Output{scale, shift, bits_out, inv_step_out, packed_out}, s);
 }
 
 int launch_forward_best(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
                         float* Y, hipStream_t s) {
-    if (forward_rows_applies(L, bits)) return launch_forward_rows(L, planes, colsum, M, bits, step, nullptr, nullptr, Y, s);
+    if (forward_rows_applies(L, bits)) return launch_forward_rows(L, planes, colsum, M, bits, step, nullptr, Y, s);
     return launch_forward(L, planes, colsum, M, bits, step, nullptr, Y, s);
 }
 
