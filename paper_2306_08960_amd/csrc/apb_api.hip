@@ -328,7 +328,6 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
         int longest = 0;
         for (int c : hcounts) longest = std::max(longest, c);
         d.rows_short = longest <= kShortRow;
-        d.rows_rich = N > 192 && nnz >= (long long)4 * N && (long long)32 * longest <= nnz;
         std::vector<uint32_t> hsign((size_t)N * d.Kw), sg((size_t)tiles * d.rows_ksteps * 64, 0u);
         APB_HIP(hipMemcpyAsync(hsign.data(), d.sign, hsign.size() * 4, hipMemcpyDeviceToHost, s));
         APB_HIP(hipStreamSynchronize(s));

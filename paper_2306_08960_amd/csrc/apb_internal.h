@@ -50,7 +50,6 @@ struct LayerDev {
     int rows_unit_log2 = 0;        // the residuals are whole multiples of 2^rows_unit_log2 ...
     int rows_windows = 1;          // ... and are cut into this many windows of kWindowBits bits
     bool rows_short = true;        // no row has more than kShortRow residuals
-    bool rows_rich = false;        // 192 rows and more that carry 4 residuals or more, in lists of similar lengths
     long long rows_steps = 0;
     uint32_t* rows_sign = nullptr; // [tiles][ksteps][64]     sign words in the order the binary part's lanes take them:
                                    //           lane (i, g): word 4 * step + g of row 16 * tile + i, the bit pairs of every

@@ -605,8 +605,10 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, const RowsParams& p
     }
 }
 
+// Four waves per SIMD at up to 128 registers; the widest items have the registers of two.
+#define APB_ROWS_ATTR __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NCW == 4 ? 2 : 4, 4)))
 template <int BITS, int SRC, bool REQ, int NT, int NCW, bool GENERAL>
-__device__ __forceinline__ void rows_task(const RowsArgs& a, const RowsParams& p) {
+__global__ APB_ROWS_ATTR void k_forward_rows(const RowsArgs a, const RowsParams p) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int waves = blockDim.x / kWave;
@@ -660,19 +662,6 @@ __device__ __forceinline__ void rows_task(const RowsArgs& a, const RowsParams& p
     }
 }
 
-// Four waves per SIMD at up to 128 registers; the widest items have the registers of two.
-#define APB_ROWS_ATTR __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NCW == 4 ? 2 : 4, 4)))
-
-// Two names for one body, so that a profile tells layers whose rows carry many residuals from the others.
-template <int BITS, int SRC, bool REQ, int NT, int NCW, bool GENERAL>
-__global__ APB_ROWS_ATTR void k_forward_rows(const RowsArgs a, const RowsParams p) {
-    rows_task<BITS, SRC, REQ, NT, NCW, GENERAL>(a, p);
-}
-template <int BITS, int SRC, bool REQ, int NT, int NCW, bool GENERAL>
-__global__ APB_ROWS_ATTR void k_forward_light_rows(const RowsArgs a, const RowsParams p) {
-    rows_task<BITS, SRC, REQ, NT, NCW, GENERAL>(a, p);
-}
-
 // The kernels address their LDS from address 0: true while they have no static LDS in front of the dynamic array.
 // Checked once per kernel and process, from the kernel's own attributes; a launch of more LDS than a kernel gets
 // without asking is asked for once per device and kernel.
@@ -705,23 +694,15 @@ int launch_kernel(const RowsArgs& a, const RowsParams& p, long long wgs, int wav
 
 bool is_general(const LayerDev& L) { return L.rows_windows > 1 || !L.rows_short || L.K > kRowsByteK; }
 
-template <int BITS, int SRC, bool REQ, int NT, int NCW, bool GENERAL>
-int launch_named(const LayerDev& L, const RowsArgs& a, const RowsParams& p, long long wgs, int waves, int lds, hipStream_t s) {
-    return L.rows_rich ? launch_kernel<k_forward_rows<BITS, SRC, REQ, NT, NCW, GENERAL>>(a, p, wgs, waves, lds, s)
-                       : launch_kernel<k_forward_light_rows<BITS, SRC, REQ, NT, NCW, GENERAL>>(a, p, wgs, waves, lds, s);
-}
-
 template <int BITS, int SRC, bool REQ>
 int launch_shape(const LayerDev& L, const RowsArgs& a, const RowsParams& p, const RowsShape& h, long long wgs, int lds, hipStream_t s) {
-    if (is_general(L)) return launch_named<BITS, SRC, REQ, 1, 1, true>(L, a, p, wgs, h.waves, lds, s);
-    switch (8 * h.nt + h.ncw) {
-        case 9: return launch_named<BITS, SRC, REQ, 1, 1, false>(L, a, p, wgs, h.waves, lds, s);
-        case 10: return launch_named<BITS, SRC, REQ, 1, 2, false>(L, a, p, wgs, h.waves, lds, s);
-        case 12: return launch_named<BITS, SRC, REQ, 1, 4, false>(L, a, p, wgs, h.waves, lds, s);
-        case 17: return launch_named<BITS, SRC, REQ, 2, 1, false>(L, a, p, wgs, h.waves, lds, s);
-        case 18: return launch_named<BITS, SRC, REQ, 2, 2, false>(L, a, p, wgs, h.waves, lds, s);
-        default: return APB_ERR_SHAPE;
-    }
+    const bool general = is_general(L);
+    if (general && h.nt == 1 && h.ncw == 1) return launch_kernel<k_forward_rows<BITS, SRC, REQ, 1, 1, true>>(a, p, wgs, h.waves, lds, s);
+    if (general) return APB_ERR_SHAPE;
+    if (h.nt == 1 && h.ncw == 1) return launch_kernel<k_forward_rows<BITS, SRC, REQ, 1, 1, false>>(a, p, wgs, h.waves, lds, s);
+    if (h.nt == 1 && h.ncw == 4) return launch_kernel<k_forward_rows<BITS, SRC, REQ, 1, 4, false>>(a, p, wgs, h.waves, lds, s);
+    if (h.nt == 2 && h.ncw == 2) return launch_kernel<k_forward_rows<BITS, SRC, REQ, 2, 2, false>>(a, p, wgs, h.waves, lds, s);
+    return APB_ERR_SHAPE;
 }
 
 int log2_of(int v) {
@@ -812,14 +793,12 @@ bool forward_rows_float_applies(const LayerDev& L, int M, int bits) {
 
 const char* forward_rows_kernel_name(const LayerDev& L, int M, int bits) {
     const RowsShape h = pick_rows_shape({L.N, M, L.rows_ksteps, bits, is_general(L), false, false});
-#define APB_NAMES(K, B) \
-    {#K "<" #B ", 0, false, 1, 1, true>", #K "<" #B ", 0, false, 1, 1, false>", #K "<" #B ", 0, false, 1, 2, false>", \
-     #K "<" #B ", 0, false, 1, 4, false>", #K "<" #B ", 0, false, 2, 2, false>"}
-    static const char* names[2][2][5] = {{APB_NAMES(k_forward_light_rows, 1), APB_NAMES(k_forward_light_rows, 2)},
-                                         {APB_NAMES(k_forward_rows, 1), APB_NAMES(k_forward_rows, 2)}};
+#define APB_NAMES(B) \
+    {"k_forward_rows<" #B ", 0, false, 1, 1, true>", "k_forward_rows<" #B ", 0, false, 1, 1, false>", \
+     "k_forward_rows<" #B ", 0, false, 1, 4, false>", "k_forward_rows<" #B ", 0, false, 2, 2, false>"}
+    static const char* names[2][4] = {APB_NAMES(1), APB_NAMES(2)};
 #undef APB_NAMES
-    const bool general = is_general(L);
-    return names[L.rows_rich ? 1 : 0][bits - 1][general ? 0 : h.nt == 2 ? 4 : h.ncw == 1 ? 1 : h.ncw == 2 ? 2 : 3];
+    return names[bits - 1][is_general(L) ? 0 : h.nt == 2 ? 3 : h.ncw == 4 ? 2 : 1];
 }
 
 int launch_forward_rows(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,

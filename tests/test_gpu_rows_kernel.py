@@ -1,10 +1,9 @@
-"""The rows-in-lanes forward kernel (lanes along the rows of the sparse matrix; layers of 256 rows and more with
-enough residuals per row) through apb_forward, against the CPU oracle: integer part exact through the separate
-entry point, every output of Y within 1e-5 relative, no floor.  Each case first checks, by the kernel name the
-library reports, that it is this kernel that runs.  Shapes: rows not a multiple of 64 (padding slots), K not a
-multiple of 128 or of 32 (padded matrix steps, partial last word), column groups with fewer than 16 valid columns,
-one column, empty rows and rows of very different lengths (padding entries in the lists), the largest K whose code
-table fits on chip, both activation widths.  Every case that runs on this kernel also runs its packed-output
+"""The matrix-core forward kernel (residuals as base-32 digits; every layer whose code table fits on chip) through
+apb_forward, against the CPU oracle: every output of Y within 1e-5 relative, no floor.  Each case first checks, by the
+kernel name the library reports, whether it is this kernel that runs.  Shapes: rows not a multiple of 16 (padding
+tiles), K not a multiple of 128 or of 32 (padded matrix steps, partial last word), column groups with fewer than 16 valid
+columns, one column, empty rows and rows of very different lengths (padding entries in the digit steps), the largest K
+whose code table fits on chip, both activation widths.  Every case that runs on this kernel also runs its packed-output
 form (apb_forward_requant) and compares the codes and column sums with the oracle's."""
 import os
 
@@ -70,14 +69,11 @@ def check(b, W, delta, X, bits, step, tag, expect_rows=True):
 
 SHAPES = [(256, 128, 16), (257, 100, 1), (300, 97, 15), (320, 1000, 17), (513, 300, 100), (640, 4100, 70),
           (1000, 257, 1000), (256, 2304, 333),
-          # a little more than four tasks per compute unit: the remainder's column groups run as the finer tail
-          # (2 and 3 row groups, the last one with idle waves, ragged M)
+          # a few more column tiles than fill the chip, ragged M
           (512, 300, 8310), (600, 200, 5590),
-          # the same with one task per compute unit and a few more: one row group (whose packed-output form stores
-          # plainly and takes no tail) and two
+          # about one workgroup per compute unit and a few more
           (256, 128, 4340), (300, 97, 2200),
-          # few column groups: one workgroup per compute unit already (no sharing), two waves per block of rows to
-          # get there, and the doubling more that long rows take
+          # many rows and few columns: the tiles are shared by several workgroups
           (4100, 500, 250), (4100, 300, 120), (4100, 4100, 250)]
 
 
@@ -86,6 +82,13 @@ SHAPES = [(256, 128, 16), (257, 100, 1), (300, 97, 15), (320, 1000, 17), (513, 3
 def test_ragged_shapes(b, N, K, M, bits):
     W, delta, X, step = synth.random_case(9000 + N + K + M + bits, N, K, M, bits, rho=0.12)
     check(b, W, delta, X, bits, step, "ragged")
+
+
+@pytest.mark.parametrize("N,K,M,bits", [(10, 500, 17000, 2), (32, 576, 25088, 1), (32, 4900, 16400, 2),    # two tiles and many columns
+                                        (512, 4864, 12544, 1)])            # tables of 152 KB beside the rows' sums
+def test_sizes_at_the_edges_of_the_launch_choice(b, N, K, M, bits):
+    W, delta, X, step = synth.random_case(9300 + N + K + bits, N, K, M, bits, rho=0.02)
+    check(b, W, delta, X, bits, step, "launch choice")
 
 
 def test_empty_rows_and_very_uneven_rows(b):
@@ -112,19 +115,18 @@ def test_largest_k_whose_table_fits_and_the_fallback_beyond(b):
         check(b, W, delta, X, 2, step, "largest K" if expect else "K beyond the table", expect_rows=expect)
 
 
-def test_layers_outside_its_range_take_the_other_kernel(b):
-    # one row carrying residuals in every column beside light rows: the lists, padded to the longest row of each
-    # block of 64, would be mostly padding
+def test_layers_of_few_rows_few_residuals_or_one_very_long_row(b):
+    # one row carrying residuals in every column beside light rows
     g = np.random.default_rng(33)
     W = (g.standard_normal((384, 700)) * 0.01).astype(np.float32)
     W[5] = 0.5
     W[::3, :8] = -0.4
     X = np.maximum(g.standard_normal((700, 90)), 0).astype(np.float32)
-    check(b, W, np.float32(0.2), X, 2, np.float32(0.75), "one very long row", expect_rows=False)
-    W, delta, X, step = synth.random_case(9200, 128, 512, 64, 2, rho=0.05)        # fewer than 4 blocks of 64 rows
-    check(b, W, delta, X, 2, step, "128 rows", expect_rows=False)
+    check(b, W, np.float32(0.2), X, 2, np.float32(0.75), "one very long row")
+    W, delta, X, step = synth.random_case(9200, 128, 512, 64, 2, rho=0.05)
+    check(b, W, delta, X, 2, step, "128 rows")
     W, delta, X, step = synth.random_case(9201, 512, 512, 64, 2, rho=0.001)       # hardly any residuals
-    check(b, W, delta, X, 2, step, "0.1 % residuals", expect_rows=False)
+    check(b, W, delta, X, 2, step, "0.1 % residuals")
 
 
 @pytest.mark.parametrize("name", ["C3_r05_b1", "C3_r50_b1", "C3_r50_b2", "C5a", "C5b"])
