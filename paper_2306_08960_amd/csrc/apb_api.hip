@@ -325,9 +325,6 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
         d.rows_windows = ds.windows;
         d.rows_unit_log2 = ds.unit;
         d.rows_steps = ds.first.back();
-        int longest = 0;
-        for (int c : hcounts) longest = std::max(longest, c);
-        d.rows_short = longest <= kShortRow;
         std::vector<uint32_t> hsign((size_t)N * d.Kw), sg((size_t)tiles * d.rows_ksteps * 64, 0u);
         APB_HIP(hipMemcpyAsync(hsign.data(), d.sign, hsign.size() * 4, hipMemcpyDeviceToHost, s));
         APB_HIP(hipStreamSynchronize(s));

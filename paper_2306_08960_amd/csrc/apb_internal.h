@@ -49,7 +49,6 @@ struct LayerDev {
     int rows_ksteps = 0;           // K in steps of 128, rounded up
     int rows_unit_log2 = 0;        // the residuals are whole multiples of 2^rows_unit_log2 ...
     int rows_windows = 1;          // ... and are cut into this many windows of kWindowBits bits
-    bool rows_short = true;        // no row has more than kShortRow residuals
     long long rows_steps = 0;
     uint32_t* rows_sign = nullptr; // [tiles][ksteps][64]     sign words in the order the binary part's lanes take them:
                                    //           lane (i, g): word 4 * step + g of row 16 * tile + i, the bit pairs of every
@@ -77,9 +76,8 @@ __host__ __device__ inline int digit_steps_of(int entries) {
     return s <= 1 ? 1 : s <= 4 ? s : s <= 6 ? 6 : (s + 3) / 4 * 4;
 }
 constexpr int kStepPad = 8;
-constexpr int kRowsByteK = 8192;
+constexpr int kRowsByteK = 8192;             // (and 3 * 16 * 33 * kRowsByteK < 2^24: see rows_item)
 constexpr int kWindowBits = 30;              // six base-32 digits, -16 .. 16
-constexpr int kShortRow = 330;               // residuals of a row whose three-digit sums stay below 2^24: 330 * 3 * 16 * (1 + 32 + 1024)
 constexpr int kRowsMaxK = 18432;             // the code table of one column group (8 bytes per value of k): 144 KB of LDS
 
 void set_last_hip_error(hipError_t e);

@@ -350,9 +350,10 @@ struct Places {
 
 // One item: NT tiles of 16 rows (from `tile` on, the workgroup's `local` and the wave's `at` th) x 16 * NCW columns from
 // column group cg0 of the table.
-// GENERAL: several windows, or rows so long that a half of six digits (three of them: up to 2^14.1 per residual) may
-// pass 2^24: windows are walked, and the digit sums are put together in integers instead of floats; also K beyond
-// kRowsByteK.
+// The sums of the three digits of a half are put together in 32-bit integers (up to 3 * 16 * 1057 per residual), after
+// the first two in a float, which is exact while 3 * 16 * 33 per residual stays below 2^24: 10592 residuals of a row,
+// more than K without GENERAL.
+// GENERAL: several windows, which are walked, or K beyond kRowsByteK.
 template <int BITS, bool REQ, int NT, int NCW, bool GENERAL>
 __device__ __forceinline__ void rows_item(const RowsArgs& a, const RowsParams& p, const Places& l, int tile, int local, int m0,
                                           int cg0, int lane) {
@@ -457,7 +458,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, const RowsParams& p
     int w = 0;
     for (int quad = 0, round = 0; quad < quads; ++quad) {
         const int S = GENERAL ? (int)cnt_at[quad] : (int)((cnt >> (8 * quad)) & 255u);
-        uint32_t t[4][NCW];
+        int t[4][NCW];
         auto run = [&](auto steps_of_pair) {
             constexpr int kS = decltype(steps_of_pair)::value;
             v4f c[NCW];
@@ -493,8 +494,8 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, const RowsParams& p
                 }
 #pragma unroll
                 for (int cg = 0; cg < NCW; ++cg)
-                    t[pr][cg] = GENERAL ? (uint32_t)((int)c[cg][0] + ((int)c[cg][1] << 5) + ((int)c[cg][2] << 10))
-                                        : __float_as_uint(fmaf(c[cg][2], 1024.0f, fmaf(c[cg][1], 32.0f, c[cg][0])));
+                    t[pr][cg] = GENERAL ? (int)c[cg][0] + ((int)c[cg][1] << 5) + ((int)c[cg][2] << 10)
+                                        : (int)fmaf(c[cg][1], 32.0f, c[cg][0]) + ((int)c[cg][2] << 10);
             });
         };
         switch (S) {                                             // (kept in step with digit_steps_of)
@@ -522,8 +523,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, const RowsParams& p
 #pragma unroll
             for (int cg = 0; cg < NCW; ++cg) {
                 const v2u x = __builtin_amdgcn_permlane16_swap(t[2 * rr][cg], t[2 * rr + 1][cg], false, false);
-                const double R = GENERAL ? fma((double)(int)x[1], 32768.0, (double)(int)x[0])
-                                         : fma((double)__uint_as_float(x[1]), 32768.0, (double)__uint_as_float(x[0]));
+                const double R = fma((double)(int)x[1], 32768.0, (double)(int)x[0]);
                 // z = step * (alpha * D + R)   (all windows but the last only add to R)
                 const float P = D[0][cg][rr];
                 const double d = BITS == 1 ? (double)(4 * (int)P - rsum - 2 * (int)cs[cg]) : (double)fmaf(2.0f, P, -cs[cg]);
@@ -692,7 +692,7 @@ int launch_kernel(const RowsArgs& a, const RowsParams& p, long long wgs, int wav
     return APB_OK;
 }
 
-bool is_general(const LayerDev& L) { return L.rows_windows > 1 || !L.rows_short || L.K > kRowsByteK; }
+bool is_general(const LayerDev& L) { return L.rows_windows > 1 || L.K > kRowsByteK; }
 
 template <int BITS, int SRC, bool REQ>
 int launch_shape(const LayerDev& L, const RowsArgs& a, const RowsParams& p, const RowsShape& h, long long wgs, int lds, hipStream_t s) {

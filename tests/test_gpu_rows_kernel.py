@@ -91,6 +91,32 @@ def test_sizes_at_the_edges_of_the_launch_choice(b, N, K, M, bits):
     check(b, W, delta, X, bits, step, "launch choice")
 
 
+@pytest.mark.parametrize("K", [331, 683, 2049, 8192, 8193, 12001])
+@pytest.mark.parametrize("bits", [1, 2])
+def test_long_rows_are_summed_exactly(b, K, bits):
+    # Every weight a residual (delta < 0, alpha = 0), values of 24 bits whose digits are as large as they get, or random
+    # ones, and the largest codes: the digit sums of a row pass 2^24, where a float would round.  The float64 sum of the
+    # reference is exact (below 2^53 units), so both sides round once and must agree to the bit.
+    g = np.random.default_rng(K + bits)
+    N, M, step = 40, 33, 0.5
+    print(f"[case] long rows K={K} bits={bits}", flush=True)
+    units = g.integers(1 << 23, 1 << 24, (N, K)) * g.choice([-1, 1], (N, K))
+    units[::4] = 0xf7bdef                                        # digits 15, 15, 15, 15, 15 (of the window's lower 25 bits)
+    units[1::4] = -0xf7bdef
+    units[2::4] = g.choice([0xf7bdef, -0xf7bdef, 0x841ef, 1], (len(units[2::4]), K))
+    W = (units.astype(np.float64) * 2.0 ** -24).astype(np.float32)
+    X = (g.standard_normal((K, M)) * 2).astype(np.float32)
+    X[:, :5] = 9.0                                               # all codes at their largest
+    code = np.where(X >= 0, 1, -1) if bits == 1 else np.clip(np.rint(X * np.float32(1 / step)), 0, 3)
+    want = (units.astype(np.float64) @ code.astype(np.float64) * (step * 2.0 ** -24)).astype(np.float32)
+    layer = b.apb_compress(torch.from_numpy(W).cuda(), -1.0, alpha=0.0)
+    name = b.apb_forward_kernel_name(layer, M, bits)
+    assert name.startswith("k_forward_rows") and name.endswith("true>" if K > 8192 else "false>"), name
+    got = b.apb_quantize_forward(layer, torch.from_numpy(X).cuda(), bits, step).cpu().numpy()
+    assert np.array_equal(got, want)
+    layer.free()
+
+
 def test_empty_rows_and_very_uneven_rows(b):
     g = np.random.default_rng(31)
     N, K, M = 384, 700, 90
