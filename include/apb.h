@@ -211,6 +211,14 @@ int apb_forward_conv3x3_requant(const apb_layer* layer, const void* fmap, int B,
  * phase). Asynchronous on `stream`. */
 int apb_forward_int(const apb_layer* layer, const void* packed, int M, int bits, int32_t* D, void* stream);
 
+/* Test hook: the operands of the matrix-core forward kernel as the layer holds them (apb_internal.h describes
+ * them), each destination NULL to skip it, device or host memory.  sizes[0]: digit steps (0: none were built, K
+ * being too large, and nothing is copied), [1]: windows, [2]: log2 of the unit, [3]: words of `sign`.  With T = 2 *
+ * ceil(N/32): first T+1 int32, count 2*T*windows bytes, steps (sizes[0] + 8) * 1408 bytes, valsum 16*T doubles.
+ * Synchronizes `stream`. */
+int apb_layer_export_steps(const apb_layer* layer, long long sizes[4], int32_t* first, uint8_t* count, uint8_t* steps,
+                           double* valsum, uint32_t* sign, void* stream);
+
 /* The same D through the paper's own formulation: xor/and + popcount over packed words
  * (Sec. IV Eq. 16 and Eqs. 18-19) on the vector ALU.  Kept as the measured comparison for the
  * matrix-core kernel and as a second, independent route to D in the tests. */

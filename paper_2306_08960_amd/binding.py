@@ -21,7 +21,7 @@ LIB_PATH = os.path.join(_HERE, "libapb.so")
 EXPORTS = (
     "apb_compress", "apb_layer_info", "apb_layer_export", "apb_layer_free", "apb_acts_bytes",
     "apb_quantize_acts", "apb_forward", "apb_forward_kernel_name", "apb_quantize_forward", "apb_quantize_forward_static", "apb_quantize_forward_is_one_kernel", "apb_forward_requant", "apb_forward_conv3x3", "apb_forward_conv3x3_requant",
-    "apb_forward_int", "apb_forward_int_popcount", "apb_forward_popcount",
+    "apb_layer_export_steps", "apb_forward_int", "apb_forward_int_popcount", "apb_forward_popcount",
     "apb_w2_pack", "apb_w2_export", "apb_w2_free", "apb_gemm_2_2_int", "apb_gemm_2_2",
     "apb_train_workspace_bytes", "apb_train_forward", "apb_train_backward",
     "apb_probe_out_bytes", "apb_probe_rate",
@@ -59,6 +59,8 @@ def load() -> ctypes.CDLL:
     lib.apb_layer_info.restype = ci
     lib.apb_layer_export.argtypes = [vp, vp, vp, vp, vp, vp, vp]
     lib.apb_layer_export.restype = ci
+    lib.apb_layer_export_steps.argtypes = [vp, ctypes.POINTER(ctypes.c_longlong * 4), vp, vp, vp, vp, vp, vp]
+    lib.apb_layer_export_steps.restype = ci
     lib.apb_layer_free.argtypes = [vp]
     lib.apb_layer_free.restype = None
     lib.apb_acts_bytes.argtypes = [ci, ci, ci]
@@ -199,6 +201,25 @@ def apb_layer_export(layer: ApbLayer, stream: Optional[torch.cuda.Stream] = None
                                    val.data_ptr(), rowsum.data_ptr(), _stream(stream)), "apb_layer_export")
     return {"sign_words": sign, "row_ptr": row_ptr, "col_idx": col[:nnz], "val": val[:nnz], "rowsum": rowsum,
             **i}
+
+
+def apb_layer_export_steps(layer: ApbLayer, stream: Optional[torch.cuda.Stream] = None) -> dict:
+    """Test hook: the operands of the matrix-core forward kernel, as GPU tensors ("steps": 0 if none were built)."""
+    sizes = (ctypes.c_longlong * 4)()
+    call, s = load().apb_layer_export_steps, _stream(stream)
+    _check(call(layer.handle, ctypes.byref(sizes), None, None, None, None, None, s), "apb_layer_export_steps")
+    steps, windows, unit, words = sizes
+    if steps == 0:
+        return {"steps": 0}
+    tiles = 2 * ((apb_layer_info(layer)["N"] + 31) // 32)
+    dev = torch.device("cuda", torch.cuda.current_device())
+    out = {"first": torch.empty(tiles + 1, dtype=torch.int32, device=dev),
+           "count": torch.empty(2 * tiles * windows, dtype=torch.uint8, device=dev),
+           "step": torch.empty(((steps + 8), 1408), dtype=torch.uint8, device=dev),
+           "valsum": torch.empty(16 * tiles, dtype=torch.float64, device=dev),
+           "sign": torch.empty(words, dtype=torch.int32, device=dev)}
+    _check(call(layer.handle, ctypes.byref(sizes), *(t.data_ptr() for t in out.values()), s), "apb_layer_export_steps")
+    return {"steps": steps, "windows": windows, "unit": unit, **out}
 
 
 def apb_acts_bytes(K: int, M: int, bits: int) -> int:

@@ -1,6 +1,5 @@
 // Host side of the C ABI: argument checks, layer ownership, launch-order row binning.
 #include <algorithm>
-#include <climits>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -24,19 +23,6 @@ void free_layer_buffers(LayerDev& d) {
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     d = LayerDev{};
-}
-
-template <typename T>
-int dev_alloc(T** p, size_t count) {
-    *p = nullptr;
-    if (count == 0) count = 1;                       // keep pointers non-null for empty CSR
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
-    if (e == hipErrorOutOfMemory) return APB_ERR_NOMEM;
-    if (e != hipSuccess) {
-        set_last_hip_error(e);
-        return APB_ERR_HIP;
-    }
-    return APB_OK;
 }
 
 // Launch-order row binning for the skewed residual counts: rows sorted by decreasing residual
@@ -108,115 +94,6 @@ void build_tile_runs(const std::vector<int32_t>& perm, const std::vector<int32_t
         }
         seg_ptr[(size_t)t * (nchunks + 1) + nchunks] = (int32_t)(ent.size() / kEntBlockWords);
     }
-}
-
-// Digit steps of the matrix-core forward kernel (see LayerDev and kStepBytes).
-struct DigitSteps {
-    int windows = 1;
-    std::vector<int32_t> first;
-    std::vector<uint8_t> count;
-    std::vector<uint8_t> step;
-    std::vector<double> valsum;
-    int unit = 0;
-};
-void build_digit_steps(int N, const std::vector<int32_t>& row_ptr, const std::vector<int32_t>& col, const std::vector<float>& val,
-                       bool bytes, DigitSteps& o) {
-    const int tiles = 2 * ((N + 31) / 32), rows = 16 * tiles;
-    int lo = 0, hi = -1;
-    bool any = false;
-    o.valsum.assign(rows, 0.0);
-    for (int n = 0; n < N; ++n)
-        for (int e = row_ptr[n]; e < row_ptr[n + 1]; ++e) {
-            o.valsum[n] += (double)val[e];
-            const float v = std::fabs(val[e]);
-            if (!(v > 0.0f) || std::isinf(v)) continue;
-            int ex;
-            const double f = std::frexp((double)v, &ex);           // v = f * 2^ex, f in [.5, 1)
-            uint32_t mant = (uint32_t)(f * 16777216.0);            // 24 bits
-            int low = ex - 24;
-            while (!(mant & 1u)) { mant >>= 1; ++low; }
-            if (!any || low < lo) lo = low;
-            if (!any || ex - 1 > hi) hi = ex - 1;
-            any = true;
-        }
-    o.windows = any ? (hi - lo + 2 + kWindowBits - 1) / kWindowBits : 1;
-    o.unit = lo;
-    const int W = o.windows;
-    o.first.assign(tiles + 1, 0);
-    o.count.assign((size_t)tiles * 2 * W, 1);
-    long long steps = 0;
-    struct Entry { int k; int q[2]; };
-    for (int quad = 0; quad < 2 * tiles; ++quad) {
-        if (quad % 2 == 0) o.first[quad / 2] = (int32_t)steps;
-        for (int w = 0; w < W; ++w) {
-            std::vector<Entry> lists[4];
-            size_t longest = 0;
-            for (int pr = 0; pr < 4; ++pr) {
-                const int ra = 16 * (quad / 2) + 2 * (quad % 2) + pr / 2 + 4 * (pr % 2), rb = ra + 8;
-                std::vector<Entry>& list = lists[pr];
-                int ea = ra < N ? row_ptr[ra] : 0, eb = rb < N ? row_ptr[rb] : 0;
-                const int eae = ra < N ? row_ptr[ra + 1] : 0, ebe = rb < N ? row_ptr[rb + 1] : 0;
-                auto digits_of = [&](float v) -> int {
-                    if (!std::isfinite(v)) v = 0.0f;
-                    double x = std::ldexp((double)v, -lo);
-                    int q = 0;
-                    for (int ww = W - 1; ww >= w; --ww) {
-                        const double qd = std::rint(std::ldexp(x, -kWindowBits * ww));
-                        x -= std::ldexp(qd, kWindowBits * ww);
-                        q = (int)qd;
-                    }
-                    return q;
-                };
-                while (ea < eae || eb < ebe) {
-                    const int ka = ea < eae ? col[ea] : INT_MAX, kb = eb < ebe ? col[eb] : INT_MAX, k = std::min(ka, kb);
-                    Entry x{k, {0, 0}};
-                    if (ka == k) x.q[0] = digits_of(val[ea++]);
-                    if (kb == k) x.q[1] = digits_of(val[eb++]);
-                    if (W == 1 || x.q[0] || x.q[1]) list.push_back(x);
-                }
-                longest = std::max(longest, list.size());
-            }
-            const int S = digit_steps_of((int)longest);
-            o.count[(size_t)quad * W + w] = (uint8_t)S;
-            for (int pr = 0; pr < 4; ++pr) {
-                    std::vector<Entry>& list = lists[pr];
-                    o.step.resize((size_t)(steps + S) * kStepBytes, 0);
-                    uint8_t* base = &o.step[(size_t)steps * kStepBytes];
-                    std::stable_sort(list.begin(), list.end(), [](const Entry& a, const Entry& b) { return (a.k & 31) < (b.k & 31); });
-                    for (int gam = 0; gam < 4 * S; ++gam) {         // a half wave's 32 rows of one gather
-                        uint8_t* st = base + (size_t)(gam >> 2) * kStepBytes;
-                        const int half = (gam >> 1) & 1, qq = gam & 1;
-                        const int k_first = gam < (int)list.size() ? list[gam].k : 0;
-                        for (int sl = 0; sl < 32; ++sl) {
-                            const size_t e = (size_t)sl * 4 * S + gam;
-                            const int g = 2 * half + (sl >> 4), i = sl & 15, tt = 16 * qq + i;
-                            const Entry x = e < list.size() ? list[e] : Entry{k_first, {0, 0}};
-                            uint16_t kk = (uint16_t)(bytes ? x.k * 8 : x.k);
-                            std::memcpy(st + kStepRows + (16 * g + i) * 4 + 2 * qq, &kk, 2);
-                            for (int hh = 0; hh < 2; ++hh) {
-                                int q = x.q[hh];
-                                for (int d = 0; d < 6; ++d) {
-                                    const int dg = d == 5 ? q : ((q + 16) & 31) - 16;
-                                    q = (q - dg) >> 5;
-                                    const uint32_t m = (uint32_t)std::abs(dg);
-                                    const uint32_t code = ((x.k & 1) == 0 ? m : m < 8 ? 2 * m : m + 8) | (dg < 0 ? 32u : 0u);
-                                    const int frag = g * 12 + hh * 6 + d;
-                                    for (int bit = 0; bit < 6; ++bit)
-                                        if ((code >> bit) & 1u) {
-                                            const int at = 6 * tt + bit;          // bit of the 192
-                                            uint8_t* p = at < 128 ? st + frag * 16 + at / 8 : st + kStepA8 + frag * 8 + (at - 128) / 8;
-                                            *p |= (uint8_t)(1u << (at & 7));
-                                        }
-                                }
-                            }
-                        }
-                    }
-                    steps += S;
-            }
-        }
-    }
-    o.first[tiles] = (int32_t)steps;
-    o.step.resize((size_t)(steps + kStepPad) * kStepBytes, 0);
 }
 
 int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStream_t s, LayerDev& d) {
@@ -298,10 +175,15 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
     if (nnz > 0 && (rc = launch_scatter_csr(W, N, K, delta, alpha, d.row_ptr, d.col_idx, d.val, d.vald, s)) != APB_OK) return rc;
     if ((rc = launch_slot_major_signs(d.sign, d.perm, d.Np, d.Kw, 2 * ((d.Kw + 1) / 2), d.signT, s)) != APB_OK) return rc;
     if ((rc = launch_slot_major_signs(d.sign, nullptr, N, d.Kw, 2 * ((d.Kw + 1) / 2), d.signC, s)) != APB_OK) return rc;
-    if ((rc = launch_slot_tables(d.perm, d.row_ptr, d.col_idx, d.val, d.Np, d.nchunks, d.chunk_ptr, d.slot_valsum,
+    const int rows = 32 * ((N + 31) / 32);             // whole words of a packed output
+    if ((rc = dev_alloc(&d.rows_valsum, (size_t)rows)) != APB_OK) return rc;
+    if ((rc = launch_row_valsum(d.row_ptr, d.val, N, rows, d.rows_valsum, s)) != APB_OK) return rc;
+    if ((rc = launch_slot_tables(d.perm, d.row_ptr, d.col_idx, d.rows_valsum, d.Np, d.nchunks, d.chunk_ptr, d.slot_valsum,
                                  s)) != APB_OK)
         return rc;
-    // Tile runs for the sparse kernel: built on the host from the CSR just written (offline work).
+    if (K <= kRowsMaxK) return build_rows_layer(d, s);   // (waits for the stream: the staging vectors may go)
+
+    // Tile runs for the sparse kernel, which takes the layers beyond: built on the host from the CSR just written.
     std::vector<int32_t> hcol((size_t)nnz);
     std::vector<float> hval((size_t)nnz);
     if (nnz > 0) {
@@ -317,36 +199,6 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
     APB_HIP(hipMemcpyAsync(d.seg_ptr, hseg.data(), hseg.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     if (!hent.empty())
         APB_HIP(hipMemcpyAsync(d.ent, hent.data(), hent.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-    if (K <= kRowsMaxK) {
-        DigitSteps ds;
-        build_digit_steps(N, hrow_ptr, hcol, hval, K <= kRowsByteK, ds);
-        const int tiles = 2 * ((N + 31) / 32);
-        d.rows_ksteps = (d.Kw + 3) / 4;
-        d.rows_windows = ds.windows;
-        d.rows_unit_log2 = ds.unit;
-        d.rows_steps = ds.first.back();
-        std::vector<uint32_t> hsign((size_t)N * d.Kw), sg((size_t)tiles * d.rows_ksteps * 64, 0u);
-        APB_HIP(hipMemcpyAsync(hsign.data(), d.sign, hsign.size() * 4, hipMemcpyDeviceToHost, s));
-        APB_HIP(hipStreamSynchronize(s));
-        for (int n = 0; n < N; ++n)
-            for (int j = 0; j < d.Kw; ++j) {
-                uint32_t w = hsign[(size_t)n * d.Kw + j];
-                const int g = j & 3;
-                if (g & 1) w = ((w & 0x33333333u) << 2) | ((w >> 2) & 0x33333333u);
-                sg[((size_t)(n / 16) * d.rows_ksteps + j / 4) * 64 + 16 * g + n % 16] = w;
-            }
-        if ((rc = dev_alloc(&d.rows_sign, sg.size())) != APB_OK) return rc;
-        if ((rc = dev_alloc(&d.rows_first, ds.first.size())) != APB_OK) return rc;
-        if ((rc = dev_alloc(&d.rows_count, ds.count.size() + 16)) != APB_OK) return rc;
-        if ((rc = dev_alloc(&d.rows_step, ds.step.size())) != APB_OK) return rc;
-        if ((rc = dev_alloc(&d.rows_valsum, ds.valsum.size())) != APB_OK) return rc;
-        APB_HIP(hipMemcpyAsync(d.rows_sign, sg.data(), sg.size() * 4, hipMemcpyHostToDevice, s));
-        APB_HIP(hipMemcpyAsync(d.rows_first, ds.first.data(), ds.first.size() * 4, hipMemcpyHostToDevice, s));
-        APB_HIP(hipMemcpyAsync(d.rows_count, ds.count.data(), ds.count.size(), hipMemcpyHostToDevice, s));
-        APB_HIP(hipMemcpyAsync(d.rows_step, ds.step.data(), ds.step.size(), hipMemcpyHostToDevice, s));
-        APB_HIP(hipMemcpyAsync(d.rows_valsum, ds.valsum.data(), ds.valsum.size() * 8, hipMemcpyHostToDevice, s));
-        APB_HIP(hipStreamSynchronize(s));
-    }
     APB_HIP(hipStreamSynchronize(s));                 // host staging vectors go out of scope after this
     return APB_OK;
 }
@@ -414,6 +266,26 @@ int apb_layer_export(const apb_layer* layer, uint32_t* sign_words, int32_t* row_
         APB_HIP(hipMemcpyAsync(col_idx, d.col_idx, (size_t)d.nnz * sizeof(int32_t), hipMemcpyDefault, s));
     if (val && d.nnz > 0) APB_HIP(hipMemcpyAsync(val, d.val, (size_t)d.nnz * sizeof(float), hipMemcpyDefault, s));
     if (rowsum) APB_HIP(hipMemcpyAsync(rowsum, d.rowsum, (size_t)d.N * sizeof(int32_t), hipMemcpyDefault, s));
+    APB_HIP(hipStreamSynchronize(s));
+    return APB_OK;
+}
+
+int apb_layer_export_steps(const apb_layer* layer, long long sizes[4], int32_t* first, uint8_t* count, uint8_t* steps,
+                           double* valsum, uint32_t* sign, void* stream) {
+    if (!layer || !sizes) return APB_ERR_NULL;
+    const LayerDev& d = layer->d;
+    const long long tiles = 2 * (((long long)d.N + 31) / 32), S = d.rows_steps;
+    sizes[0] = S;
+    sizes[1] = S ? d.rows_windows : 0;
+    sizes[2] = S ? d.rows_unit_log2 : 0;
+    sizes[3] = S ? tiles * d.rows_ksteps * 64 : 0;
+    if (S == 0) return APB_OK;
+    hipStream_t s = as_stream(stream);
+    if (first) APB_HIP(hipMemcpyAsync(first, d.rows_first, (size_t)(tiles + 1) * 4, hipMemcpyDefault, s));
+    if (count) APB_HIP(hipMemcpyAsync(count, d.rows_count, (size_t)(2 * tiles * d.rows_windows), hipMemcpyDefault, s));
+    if (steps) APB_HIP(hipMemcpyAsync(steps, d.rows_step, (size_t)(S + kStepPad) * kStepBytes, hipMemcpyDefault, s));
+    if (valsum) APB_HIP(hipMemcpyAsync(valsum, d.rows_valsum, (size_t)(16 * tiles) * 8, hipMemcpyDefault, s));
+    if (sign) APB_HIP(hipMemcpyAsync(sign, d.rows_sign, (size_t)sizes[3] * 4, hipMemcpyDefault, s));
     APB_HIP(hipStreamSynchronize(s));
     return APB_OK;
 }

@@ -157,11 +157,11 @@ __global__ __launch_bounds__(kBlock) void k_w2_pack(const float* __restrict__ W,
 }
 
 // chunk_ptr[c][i]: index of the first residual of the row in slot i whose column is >= 256*c
-// (lower bound in the ascending column list); slot_valsum[i]: float64 sum of that row's residuals.
+// (lower bound in the ascending column list); slot_valsum[i]: that row's sum of residuals.
 __global__ __launch_bounds__(kBlock) void k_slot_tables(const int32_t* __restrict__ perm,
                                                         const int32_t* __restrict__ row_ptr,
                                                         const int32_t* __restrict__ col_idx,
-                                                        const float* __restrict__ val, int Np, int nchunks,
+                                                        const double* __restrict__ row_valsum, int Np, int nchunks,
                                                         int32_t* __restrict__ chunk_ptr,
                                                         double* __restrict__ slot_valsum) {
     const long long t = (long long)blockIdx.x * kBlock + threadIdx.x;
@@ -174,11 +174,7 @@ __global__ __launch_bounds__(kBlock) void k_slot_tables(const int32_t* __restric
         return;
     }
     int lo = row_ptr[n], hi = row_ptr[n + 1];
-    if (c == 0) {
-        double sum = 0.0;
-        for (int q = lo; q < hi; ++q) sum += (double)val[q];
-        slot_valsum[i] = sum;
-    }
+    if (c == 0) slot_valsum[i] = row_valsum[n];
     const int bound = c * kChunkK;
     while (lo < hi) {
         const int mid = lo + (hi - lo) / 2;
@@ -189,11 +185,11 @@ __global__ __launch_bounds__(kBlock) void k_slot_tables(const int32_t* __restric
 
 }  // namespace
 
-int launch_slot_tables(const int32_t* perm, const int32_t* row_ptr, const int32_t* col_idx, const float* val, int Np,
+int launch_slot_tables(const int32_t* perm, const int32_t* row_ptr, const int32_t* col_idx, const double* row_valsum, int Np,
                        int nchunks, int32_t* chunk_ptr, double* slot_valsum, hipStream_t s) {
     const long long total = (long long)Np * (nchunks + 1);
     hipLaunchKernelGGL(k_slot_tables, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, perm,
-                       row_ptr, col_idx, val, Np, nchunks, chunk_ptr, slot_valsum);
+                       row_ptr, col_idx, row_valsum, Np, nchunks, chunk_ptr, slot_valsum);
     APB_HIP(hipGetLastError());
     return APB_OK;
 }

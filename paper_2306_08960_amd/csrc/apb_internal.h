@@ -38,7 +38,7 @@ struct LayerDev {
     int32_t* rowsum = nullptr;   // [N]
     int32_t* chunk_ptr = nullptr;  // [nchunks+1][Np]  first residual of slot i with column >= 256*c
     double* slot_valsum = nullptr; // [Np]             sum of the residuals of slot i (float64)
-    // Residuals regrouped for the sparse kernel: one flat run per (tile of kRowTile slots, chunk of
+    // Residuals regrouped for the sparse kernel (layers of K > kRowsMaxK only): one flat run per (tile of kRowTile slots, chunk of
     // 256 columns), sorted by row inside the run, in blocks of 8 entries.
     int32_t* seg_ptr = nullptr;    // [Np/kRowTile][nchunks+1]  first block of (tile, chunk)
     uint32_t* ent = nullptr;       // [blocks][24]  8 keys: 2 * row_in_tile | (col - 256*chunk) << 8, then
@@ -114,6 +114,19 @@ __device__ __forceinline__ uint32_t push_bit(uint32_t word, uint32_t bits) { ret
         }                                             \
     } while (0)
 
+template <typename T>
+int dev_alloc(T** p, size_t count) {
+    *p = nullptr;
+    if (count == 0) count = 1;                       // keep pointers non-null for empty CSR
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+    if (e == hipErrorOutOfMemory) return APB_ERR_NOMEM;
+    if (e != hipSuccess) {
+        set_last_hip_error(e);
+        return APB_ERR_HIP;
+    }
+    return APB_OK;
+}
+
 // ---- kernel launchers (each returns an apb_status) ------------------------------------------
 
 // compress
@@ -125,8 +138,11 @@ int launch_scatter_csr(const float* W, int N, int K, float delta, float alpha, c
                        int32_t* col_idx, float* val, double* vald, hipStream_t s);
 int launch_slot_major_signs(const uint32_t* sign, const int32_t* perm, int Np, int Kw, int rows_out,
                             uint32_t* signT, hipStream_t s);
-int launch_slot_tables(const int32_t* perm, const int32_t* row_ptr, const int32_t* col_idx, const float* val, int Np,
+int launch_slot_tables(const int32_t* perm, const int32_t* row_ptr, const int32_t* col_idx, const double* row_valsum, int Np,
                        int nchunks, int32_t* chunk_ptr, double* slot_valsum, hipStream_t s);
+int launch_row_valsum(const int32_t* row_ptr, const float* val, int N, int rows, double* valsum, hipStream_t s);
+// everything of LayerDev that begins with rows_ but for rows_valsum, from the sign words and the CSR; waits for the stream
+int build_rows_layer(LayerDev& d, hipStream_t s);
 
 // activations.  colsum == nullptr: the planes only (for a consumer that adds the code sums up from the words itself)
 int launch_quantize(const float* X, int K, int M, int bits, float inv_step, uint32_t* planes, int32_t* colsum,
