@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "apb_internal.h"
+#include "apb_rows_shape.h"
 
 namespace apb {
 
@@ -181,9 +182,10 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
     if ((rc = launch_slot_tables(d.perm, d.row_ptr, d.col_idx, d.rows_valsum, d.Np, d.nchunks, d.chunk_ptr, d.slot_valsum,
                                  s)) != APB_OK)
         return rc;
-    if (K <= kRowsMaxK) return build_rows_layer(d, s);   // (waits for the stream: the staging vectors may go)
+    if (K <= kRowsMaxK && (rc = build_rows_layer(d, s)) != APB_OK) return rc;
+    if (K <= kRowsMaxK && !columns_kernel_possible(N, K, nnz)) return APB_OK;   // (it waited: the staging vectors may go)
 
-    // Tile runs for the sparse kernel, which takes the layers beyond: built on the host from the CSR just written.
+    // Tile runs for the columns-in-lanes kernel: built on the host from the CSR just written.
     std::vector<int32_t> hcol((size_t)nnz);
     std::vector<float> hval((size_t)nnz);
     if (nnz > 0) {
@@ -355,7 +357,7 @@ int apb_forward_requant(const apb_layer* layer, const void* packed, int M, int b
     const int32_t* colsum = reinterpret_cast<const int32_t*>(planes + (size_t)bits * d.Kw * Mp);
     hipStream_t s = as_stream(stream);
     uint32_t* out = static_cast<uint32_t*>(packed_out);
-    if (forward_rows_applies(d, bits))
+    if (!takes_columns_kernel(d, M, bits, true))
         return launch_forward_rows_requant(d, planes, colsum, M, bits, step, nullptr, scale, shift, bits_out, 1.0f / step_out,
                                            out, s);
     return launch_forward_requant(d, planes, colsum, M, bits, step, nullptr, scale, shift, bits_out, 1.0f / step_out, out, s);
@@ -363,13 +365,13 @@ int apb_forward_requant(const apb_layer* layer, const void* packed, int M, int b
 
 const char* apb_forward_kernel_name(const apb_layer* layer, int M, int bits) {
     if (!layer || M <= 0 || (bits != 1 && bits != 2)) return "";
-    if (forward_rows_applies(layer->d, bits)) return forward_rows_kernel_name(layer->d, M, bits);
+    if (!takes_columns_kernel(layer->d, M, bits, false)) return forward_rows_kernel_name(layer->d, M, bits);
     return forward_kernel_name(layer->d, M, bits);
 }
 
 int apb_quantize_forward_is_one_kernel(const apb_layer* layer, int M, int bits) {
     if (!layer || M <= 0 || (bits != 1 && bits != 2)) return 0;
-    return forward_rows_float_applies(layer->d, M, bits) ? 1 : 0;
+    return step_is_one_kernel(layer->d, M, bits) ? 1 : 0;
 }
 
 int apb_quantize_forward(const apb_layer* layer, const float* X, int M, int bits, float step, void* packed, float* Y,
@@ -380,7 +382,7 @@ int apb_quantize_forward(const apb_layer* layer, const float* X, int M, int bits
     if (bits != 1 && bits != 2) return APB_ERR_BITS;
     if (!std::isfinite(step) || !(step > 0.0f)) return APB_ERR_VALUE;
     hipStream_t s = as_stream(stream);
-    if (forward_rows_float_applies(d, M, bits)) return launch_forward_rows_float(d, X, M, bits, step, Y, s);
+    if (step_is_one_kernel(d, M, bits)) return launch_step_one_kernel(d, X, M, bits, step, Y, s);
     uint32_t* planes = static_cast<uint32_t*>(packed);
     int32_t* colsum = reinterpret_cast<int32_t*>(planes + (size_t)bits * d.Kw * ((size_t)kWave * (((size_t)M + kWave - 1) / kWave)));
     return launch_quantize_then_forward(d, X, M, bits, step, planes, colsum, Y, s);
@@ -417,7 +419,7 @@ int apb_forward_conv3x3(const apb_layer* layer, const void* fmap, int B, int H, 
     hipStream_t s = as_stream(stream);
     const uint32_t* planes = static_cast<const uint32_t*>(fmap);
     const int32_t* pixsum = reinterpret_cast<const int32_t*>(planes + (size_t)bits * (conv.C / 32) * conv.Pp_in);
-    if (forward_rows_applies(d, bits))
+    if (!takes_columns_kernel(d, P, bits, false))
         return launch_forward_rows(d, planes, nullptr, P, bits, step, &conv, Y, s);
     return launch_forward(d, planes, pixsum, P, bits, step, &conv, Y, s);
 }
@@ -437,7 +439,7 @@ int apb_forward_conv3x3_requant(const apb_layer* layer, const void* fmap, int B,
     const int32_t* pixsum = reinterpret_cast<const int32_t*>(planes + (size_t)bits * (conv.C / 32) * conv.Pp_in);
     hipStream_t s = as_stream(stream);
     uint32_t* out = static_cast<uint32_t*>(fmap_out);
-    if (forward_rows_applies(d, bits))
+    if (!takes_columns_kernel(d, P, bits, true))
         return launch_forward_rows_requant(d, planes, nullptr, P, bits, step, &conv, scale, shift, bits_out, 1.0f / step_out,
                                            out, s);
     return launch_forward_requant(d, planes, pixsum, P, bits, step, &conv, scale, shift, bits_out, 1.0f / step_out, out, s);

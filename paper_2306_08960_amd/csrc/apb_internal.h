@@ -38,7 +38,7 @@ struct LayerDev {
     int32_t* rowsum = nullptr;   // [N]
     int32_t* chunk_ptr = nullptr;  // [nchunks+1][Np]  first residual of slot i with column >= 256*c
     double* slot_valsum = nullptr; // [Np]             sum of the residuals of slot i (float64)
-    // Residuals regrouped for the sparse kernel (layers of K > kRowsMaxK only): one flat run per (tile of kRowTile slots, chunk of
+    // Residuals regrouped for the columns-in-lanes kernel (layers that it may serve only, null otherwise): one flat run per (tile of kRowTile slots, chunk of
     // 256 columns), sorted by row inside the run, in blocks of 8 entries.
     int32_t* seg_ptr = nullptr;    // [Np/kRowTile][nchunks+1]  first block of (tile, chunk)
     uint32_t* ent = nullptr;       // [blocks][24]  8 keys: 2 * row_in_tile | (col - 256*chunk) << 8, then
@@ -181,14 +181,21 @@ bool forward_rows_applies(const LayerDev& L, int bits);
 const char* forward_rows_kernel_name(const LayerDev& L, int M, int bits);
 int launch_forward_rows(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
                         const ConvShape* conv, float* Y, hipStream_t s);
-// from the float matrix X (K x M), quantize + forward in one kernel: same Y, bit for bit, as launch_quantize +
-// launch_forward_rows; only where forward_rows_float_applies says so (APB_ERR_SHAPE otherwise)
-bool forward_rows_float_applies(const LayerDev& L, int M, int bits);
-int launch_forward_rows_float(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s);
 // ending in the next layer's quantizer (see launch_forward_requant)
 int launch_forward_rows_requant(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
                                 const ConvShape* conv, const float* scale, const float* shift, int bits_out,
                                 float inv_step_out, uint32_t* packed_out, hipStream_t s);
+// the one-kernel step with the columns in the lanes (apb_sparse.hip), where it is possible
+bool forward_float_applies(const LayerDev& L, int M, int bits);
+int launch_forward_float(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s);
+
+// Which of the two forward kernels a call takes: the columns-in-lanes kernel (apb_sparse.hip) for layers the other has no
+// operands for, and where it is the faster one.
+bool takes_columns_kernel(const LayerDev& L, int M, int bits, bool packed_out);
+// from the float matrix X (K x M), quantize + forward in one kernel: same Y, bit for bit, as launch_quantize +
+// launch_forward_best; only where step_is_one_kernel says so (APB_ERR_SHAPE otherwise)
+bool step_is_one_kernel(const LayerDev& L, int M, int bits);
+int launch_step_one_kernel(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s);
 // launch_quantize + launch_forward_best through the scratch buffer planes / colsum (the step of layers that do
 // not run as one kernel); what `colsum` holds afterwards is unspecified
 int launch_quantize_then_forward(const LayerDev& L, const float* X, int M, int bits, float step, uint32_t* planes,

@@ -46,7 +46,7 @@ extern "C" int apb_quantize_forward_static(const apb_layer* layer, const float* 
     const size_t need = sizeof(uint32_t) * Mp * ((size_t)bits * d.Kw + 1);    // = apb_acts_bytes(K, M, bits)
     if (need > (size_t)APB_STATIC_SCRATCH_BYTES) return APB_ERR_SCRATCH;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (forward_rows_float_applies(d, M, bits)) return launch_forward_rows_float(d, X, M, bits, step, Y, s);   // one kernel, no scratch
+    if (step_is_one_kernel(d, M, bits)) return launch_step_one_kernel(d, X, M, bits, step, Y, s);   // no scratch
     void* base = nullptr;
     int rc = scratch_of_current_device(&base);
     if (rc != APB_OK) return rc;

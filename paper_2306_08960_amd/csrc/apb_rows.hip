@@ -721,7 +721,7 @@ struct Output {
 
 int launch_any(const LayerDev& L, const void* src, Source kind, const int32_t* colsum, int M, int bits, float step,
                const ConvShape* conv, const Output& o, hipStream_t s) {
-    if (kind == kFloat ? !forward_rows_float_applies(L, M, bits) : !forward_rows_applies(L, bits)) return APB_ERR_SHAPE;
+    if (!forward_rows_applies(L, bits) || (kind == kFloat && !rows_from_float(L.N, L.K, M))) return APB_ERR_SHAPE;
     const long long Mp = (long long)kWave * (((long long)M + kWave - 1) / kWave);
     if (Mp * 8 >= (1LL << 31)) return APB_ERR_SHAPE;
     const bool req = o.bits != 0;
@@ -787,8 +787,14 @@ bool forward_rows_applies(const LayerDev& L, int bits) {
     return L.rows_steps > 0 && mfma_sum_exact(L.K, 1, bits == 1 ? 1 : 3);
 }
 
-bool forward_rows_float_applies(const LayerDev& L, int M, int bits) {
-    return forward_rows_applies(L, bits) && rows_from_float(L.N, L.K, M);
+bool step_is_one_kernel(const LayerDev& L, int M, int bits) {
+    return takes_columns_kernel(L, M, bits, false) ? forward_float_applies(L, M, bits) : rows_from_float(L.N, L.K, M);
+}
+
+int launch_step_one_kernel(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s) {
+    if (!step_is_one_kernel(L, M, bits)) return APB_ERR_SHAPE;
+    if (takes_columns_kernel(L, M, bits, false)) return launch_forward_float(L, X, M, bits, step, Y, s);
+    return launch_any(L, X, kFloat, nullptr, M, bits, step, nullptr, Output{nullptr, nullptr, 0, 0.0f, Y}, s);
 }
 
 const char* forward_rows_kernel_name(const LayerDev& L, int M, int bits) {
@@ -807,10 +813,6 @@ int launch_forward_rows(const LayerDev& L, const uint32_t* planes, const int32_t
                       Output{nullptr, nullptr, 0, 0.0f, Y}, s);
 }
 
-int launch_forward_rows_float(const LayerDev& L, const float* X, int M, int bits, float step, float* Y, hipStream_t s) {
-    return launch_any(L, X, kFloat, nullptr, M, bits, step, nullptr, Output{nullptr, nullptr, 0, 0.0f, Y}, s);
-}
-
 int launch_forward_rows_requant(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
                                 const ConvShape* conv, const float* scale, const float* shift, int bits_out,
                                 float inv_step_out, uint32_t* packed_out, hipStream_t s) {
@@ -818,9 +820,14 @@ int launch_forward_rows_requant(const LayerDev& L, const uint32_t* planes, const
                       Output{scale, shift, bits_out, inv_step_out, packed_out}, s);
 }
 
+bool takes_columns_kernel(const LayerDev& L, int M, int bits, bool packed_out) {
+    if (!forward_rows_applies(L, bits)) return true;
+    return L.ent && columns_kernel_better(L.N, L.K, L.nnz, M, packed_out);
+}
+
 int launch_forward_best(const LayerDev& L, const uint32_t* planes, const int32_t* colsum, int M, int bits, float step,
                         float* Y, hipStream_t s) {
-    if (forward_rows_applies(L, bits)) return launch_forward_rows(L, planes, colsum, M, bits, step, nullptr, Y, s);
+    if (!takes_columns_kernel(L, M, bits, false)) return launch_forward_rows(L, planes, colsum, M, bits, step, nullptr, Y, s);
     return launch_forward(L, planes, colsum, M, bits, step, nullptr, Y, s);
 }
 
@@ -828,7 +835,7 @@ int launch_quantize_then_forward(const LayerDev& L, const float* X, int M, int b
                                  int32_t* colsum, float* Y, hipStream_t s) {
     // This kernel reads every word of its columns anyway and adds their code sums up itself: the quantize kernel then
     // writes the planes only -- no sums in LDS, and where it splits K no fill launch and no atomics.
-    const bool rows = forward_rows_applies(L, bits);
+    const bool rows = !takes_columns_kernel(L, M, bits, false);
     const int rc = launch_quantize(X, L.K, M, bits, 1.0f / step, planes, rows ? nullptr : colsum, s);
     if (rc != APB_OK) return rc;
     return launch_forward_best(L, planes, rows ? nullptr : colsum, M, bits, step, Y, s);

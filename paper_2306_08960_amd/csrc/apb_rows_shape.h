@@ -31,6 +31,28 @@ struct RowsShape {
 // Tiles of 16 rows: an even number, so that two of them make a word of a packed output.
 inline int rows_tiles(int N) { return 2 * (N / 32 + (N % 32 != 0)); }
 
+// Where the columns-in-lanes kernel (apb_sparse.hip) is the faster one: few residuals per row and many outputs.  There a
+// residual costs four instructions for 64 columns; here a pair of rows takes at least one digit step, of which a layer of 6
+// residuals per row fills a tenth, and the epilogue of a short K weighs more than its products.  Residuals per row up
+// to which it wins, fitted to both kernels over K 96 .. 1152, N 32 .. 512, M 8192 .. 131072 and 1 .. 24 residuals per
+// row (N = 64, K = 288, M = 131072, 6 per row: the step 48 us here, 39 there, packed output 22 and 18; K = 576, 12
+// per row: 72 and 64; N = 64, K = 1152, M = 50176, 6 per row: 53 and 54, 16 and 18).  A packed output of more than 128
+// rows takes it atomics.  The rule looks at nothing but sizes and the kind of output: a step gives the same bits as
+// its two calls.
+inline double columns_kernel_residuals(int N, int K, int M, bool packed_out) {
+    if (packed_out) return N <= 128 && M >= 40000 ? 12.0 - K / 96.0 : -1.0;
+    if (N <= 32 || (N <= 64 && M < 90000)) return M >= 60000 ? 12.0 - K / 64.0 : -1.0;
+    if ((long long)N * M < 4000000) return -1.0;
+    return N <= 128 ? 20.0 - K / 96.0 : 8.0 - K / 200.0;
+}
+inline bool columns_kernel_better(int N, int K, long long nnz, int M, bool packed_out) {
+    return (double)nnz <= columns_kernel_residuals(N, K, M, packed_out) * N;
+}
+inline bool columns_kernel_possible(int N, int K, long long nnz) {     // for some M
+    const int most = 0x7fffffff;
+    return columns_kernel_better(N, K, nnz, most, false) || columns_kernel_better(N, K, nnz, most, true);
+}
+
 // Quantize + forward in one kernel: where one workgroup holds every row of the layer, so that no column of X is
 // quantized twice, and the columns fill the chip (a narrow tail of them would read X with too few waves); and where X is
 // so small (a quarter of a MB: every workgroup's share comes from the L2) that the launches saved are worth more.

@@ -18,6 +18,9 @@ static void check(int N, int K, int M, int bits, bool general, bool packed_out, 
     if ((long long)N * M >= (1LL << 40) || (long long)N * K >= (1LL << 31)) return;
     if (from_float && (packed_out || !rows_from_float(N, K, M))) return;
     if (K > 8192 && !general) return;
+    for (long long nnz : {0LL, 1LL * N, 5LL * N, 11LL * N, 18LL * N})     // (a layer gets the operands of the kernel it may be given to)
+        if (columns_kernel_better(N, K, nnz, M, packed_out) && !columns_kernel_possible(N, K, nnz) && ++bad <= 20)
+            std::printf("no tile runs: N=%d K=%d M=%d nnz=%lld\n", N, K, M, nnz);
     const RowsProblem q{N, M, (K + 127) / 128, bits, general, packed_out, from_float};
     const RowsShape h = pick_rows_shape(q);
     ++seen;
