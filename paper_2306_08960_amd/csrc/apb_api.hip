@@ -19,9 +19,7 @@ namespace {
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 void free_layer_buffers(LayerDev& d) {
-    void* ptrs[] = {d.sign, d.signT, d.perm, d.row_ptr, d.col_idx, d.val, d.rowsum, d.chunk_ptr, d.slot_valsum, d.vald, d.signC,
-                    d.seg_ptr, d.ent, d.rows_sign, d.rows_first, d.rows_count, d.rows_step, d.rows_valsum};
-    for (void* p : ptrs)
+    for (void* p : d.blocks)
         if (p) (void)hipFree(p);
     d = LayerDev{};
 }
@@ -51,14 +49,15 @@ std::vector<int32_t> balanced_slots(const std::vector<int32_t>& counts, int Np) 
 // Regroup the CSR for the sparse kernel: for every tile of kRowTile launch slots and every chunk of
 // kChunkK columns one flat run of entries, sorted by (row in tile, column) and padded to whole
 // blocks of 8.  A block is 24 words: 8 keys (2*row | column_in_chunk << 8), then the 8 residuals as
-// float64 times 2^kEntValScaleLog2; padding entries have key 0 and value 0.  seg_ptr counts blocks.
-void build_tile_runs(const std::vector<int32_t>& perm, const std::vector<int32_t>& row_ptr,
-                     const std::vector<int32_t>& col, const std::vector<float>& val, int nchunks,
-                     std::vector<int32_t>& seg_ptr, std::vector<uint32_t>& ent) {
+// float64 times 2^kEntValScaleLog2; padding entries have key 0 and value 0.  seg_ptr, which counts blocks, lies at the
+// front of `out`, the blocks from word ent_at on.
+void build_tile_runs(const std::vector<int32_t>& perm, const std::vector<int32_t>& row_ptr, const int32_t* col, const float* val, long long nnz,
+                     int nchunks, std::vector<uint32_t>& out, size_t& ent_at) {
     const int tiles = (int)perm.size() / kRowTile;
-    seg_ptr.assign((size_t)tiles * (nchunks + 1), 0);
-    ent.clear();
-    ent.reserve(col.size() * 3 + 24);
+    ent_at = ((size_t)tiles * (nchunks + 1) + 63) / 64 * 64;
+    out.reserve(ent_at + (size_t)nnz * 4 + 64);
+    out.assign(ent_at, 0u);
+    auto blocks = [&] { return (uint32_t)((out.size() - ent_at) / kEntBlockWords); };
     std::vector<int32_t> cursor(kRowTile);
     std::vector<uint32_t> key;
     std::vector<double> dval;
@@ -68,7 +67,7 @@ void build_tile_runs(const std::vector<int32_t>& perm, const std::vector<int32_t
             cursor[r] = n >= 0 ? row_ptr[n] : 0;
         }
         for (int c = 0; c < nchunks; ++c) {
-            seg_ptr[(size_t)t * (nchunks + 1) + c] = (int32_t)(ent.size() / kEntBlockWords);
+            out[(size_t)t * (nchunks + 1) + c] = blocks();
             const int hi = (c + 1) * kChunkK;
             key.clear();
             dval.clear();
@@ -87,13 +86,13 @@ void build_tile_runs(const std::vector<int32_t>& perm, const std::vector<int32_t
                 dval.push_back(0.0);
             }
             for (size_t b = 0; b < key.size(); b += 8) {
-                const size_t at = ent.size();
-                ent.resize(at + kEntBlockWords);
-                std::memcpy(&ent[at], &key[b], 8 * sizeof(uint32_t));
-                std::memcpy(&ent[at + 8], &dval[b], 8 * sizeof(double));
+                const size_t at = out.size();
+                out.resize(at + kEntBlockWords);
+                std::memcpy(&out[at], &key[b], 8 * sizeof(uint32_t));
+                std::memcpy(&out[at + 8], &dval[b], 8 * sizeof(double));
             }
         }
-        seg_ptr[(size_t)t * (nchunks + 1) + nchunks] = (int32_t)(ent.size() / kEntBlockWords);
+        out[(size_t)t * (nchunks + 1) + nchunks] = blocks();
     }
 }
 
@@ -106,60 +105,54 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
     const int rows_per_block = kRowTile * d.waves;
     d.Np = rows_per_block * ((N + rows_per_block - 1) / rows_per_block);
     d.nchunks = (d.Kw + kChunkWords - 1) / kChunkWords;
-    int rc;
+    const bool digits = K <= kRowsMaxK;
+    const int Kw2 = 2 * ((d.Kw + 1) / 2), rows = 32 * ((N + 31) / 32);   // (whole words of a packed output)
+    constexpr int kParts = 1024;
+    double* parts = nullptr;
+    int32_t *counts = nullptr, *found = nullptr;
+    DeviceArrays fixed;
+    fixed.add(&parts, 2 * kParts);
+    fixed.add(&counts, (size_t)N);
+    fixed.add(&found, digit_scratch_words(N));
+    fixed.add(&d.sign, (size_t)N * d.Kw);
+    fixed.add(&d.rowsum, (size_t)N);
+    fixed.add(&d.row_ptr, (size_t)N + 1 + d.Np);       // and perm
+    fixed.add(&d.signT, (size_t)d.Np * Kw2);
+    fixed.add(&d.signC, (size_t)N * Kw2);
+    fixed.add(&d.chunk_ptr, (size_t)d.Np * (d.nchunks + 1));
+    fixed.add(&d.slot_valsum, (size_t)d.Np);
+    fixed.add(&d.rows_valsum, (size_t)rows);
+    d.rows_ksteps = (d.Kw + 3) / 4;
+    fixed.add(&d.rows_sign, digits ? (size_t)rows / 16 * d.rows_ksteps * 64 : 0);
+    int rc = fixed.alloc(&d.blocks[0]);
+    if (rc != APB_OK) return rc;
+    d.perm = d.row_ptr + N + 1;
 
     if (std::isnan(alpha)) {                          // default scale: mean |w| over the binarized set
-        constexpr int kParts = 1024;
-        double* part_sum = nullptr;
-        long long* part_cnt = nullptr;
-        if ((rc = dev_alloc(&part_sum, kParts)) != APB_OK) return rc;
-        if ((rc = dev_alloc(&part_cnt, kParts)) != APB_OK) {
-            (void)hipFree(part_sum);
-            return rc;
-        }
-        std::vector<double> hs(kParts);
-        std::vector<long long> hc(kParts);
-        rc = launch_inlier_abs_sum(W, (long long)N * K, delta, part_sum, part_cnt, kParts, s);
-        hipError_t e = hipSuccess;
-        if (rc == APB_OK) e = hipMemcpyAsync(hs.data(), part_sum, kParts * sizeof(double), hipMemcpyDeviceToHost, s);
-        if (rc == APB_OK && e == hipSuccess)
-            e = hipMemcpyAsync(hc.data(), part_cnt, kParts * sizeof(long long), hipMemcpyDeviceToHost, s);
-        if (rc == APB_OK && e == hipSuccess) e = hipStreamSynchronize(s);
-        (void)hipFree(part_sum);
-        (void)hipFree(part_cnt);
-        if (rc != APB_OK) return rc;
-        APB_HIP(e);
+        static_assert(sizeof(long long) == sizeof(double), "sums and counts share an array");
+        long long* part_cnt = reinterpret_cast<long long*>(parts + kParts);
+        std::vector<double> h(2 * kParts);
+        if ((rc = launch_inlier_abs_sum(W, (long long)N * K, delta, parts, part_cnt, kParts, s)) != APB_OK) return rc;
+        APB_HIP(hipMemcpyAsync(h.data(), parts, 2 * kParts * sizeof(double), hipMemcpyDeviceToHost, s));
+        APB_HIP(hipStreamSynchronize(s));
         double total = 0.0;
         long long cnt = 0;
         for (int i = 0; i < kParts; ++i) {
-            total += hs[i];
-            cnt += hc[i];
+            long long c;
+            std::memcpy(&c, &h[kParts + i], sizeof(c));
+            total += h[i];
+            cnt += c;
         }
         alpha = cnt > 0 ? (float)(total / (double)cnt) : 0.0f;
     }
     d.alpha = alpha;
 
-    int32_t* counts = nullptr;
-    if ((rc = dev_alloc(&d.sign, (size_t)N * d.Kw)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.rowsum, (size_t)N)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.row_ptr, (size_t)N + 1)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.perm, (size_t)d.Np)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.signT, (size_t)d.Np * (2 * ((d.Kw + 1) / 2)))) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.signC, (size_t)N * (2 * ((d.Kw + 1) / 2)))) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.chunk_ptr, (size_t)d.Np * (d.nchunks + 1))) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.slot_valsum, (size_t)d.Np)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&counts, (size_t)N)) != APB_OK) return rc;
-
     std::vector<int32_t> hcounts(N);
-    rc = launch_sign_pack_count(W, N, K, d.Kw, delta, d.sign, counts, d.rowsum, s);
-    hipError_t e = hipSuccess;
-    if (rc == APB_OK) e = hipMemcpyAsync(hcounts.data(), counts, (size_t)N * sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (rc == APB_OK && e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(counts);
-    if (rc != APB_OK) return rc;
-    APB_HIP(e);
+    if ((rc = launch_sign_pack_count(W, N, K, d.Kw, delta, d.sign, counts, d.rowsum, s)) != APB_OK) return rc;
+    APB_HIP(hipMemcpyAsync(hcounts.data(), counts, (size_t)N * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    APB_HIP(hipStreamSynchronize(s));
 
-    std::vector<int32_t> hrow_ptr((size_t)N + 1, 0);
+    std::vector<int32_t> hrow_ptr((size_t)N + 1 + d.Np, 0);
     long long nnz = 0;
     for (int n = 0; n < N; ++n) {
         nnz += hcounts[n];
@@ -167,40 +160,40 @@ int compress_impl(const float* W, int N, int K, float delta, float alpha, hipStr
     }
     d.nnz = nnz;
     const std::vector<int32_t> hperm = balanced_slots(hcounts, d.Np);
+    std::copy(hperm.begin(), hperm.end(), hrow_ptr.begin() + N + 1);
 
-    if ((rc = dev_alloc(&d.col_idx, (size_t)nnz)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.val, (size_t)nnz)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.vald, (size_t)nnz)) != APB_OK) return rc;
-    APB_HIP(hipMemcpyAsync(d.row_ptr, hrow_ptr.data(), ((size_t)N + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    APB_HIP(hipMemcpyAsync(d.perm, hperm.data(), (size_t)d.Np * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    DeviceArrays csr;
+    csr.add(&d.col_idx, (size_t)nnz);
+    csr.add(&d.val, (size_t)nnz);
+    csr.add(&d.vald, (size_t)nnz);
+    if ((rc = csr.alloc(&d.blocks[1])) != APB_OK) return rc;
+    APB_HIP(hipMemcpyAsync(d.row_ptr, hrow_ptr.data(), hrow_ptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     if (nnz > 0 && (rc = launch_scatter_csr(W, N, K, delta, alpha, d.row_ptr, d.col_idx, d.val, d.vald, s)) != APB_OK) return rc;
-    if ((rc = launch_slot_major_signs(d.sign, d.perm, d.Np, d.Kw, 2 * ((d.Kw + 1) / 2), d.signT, s)) != APB_OK) return rc;
-    if ((rc = launch_slot_major_signs(d.sign, nullptr, N, d.Kw, 2 * ((d.Kw + 1) / 2), d.signC, s)) != APB_OK) return rc;
-    const int rows = 32 * ((N + 31) / 32);             // whole words of a packed output
-    if ((rc = dev_alloc(&d.rows_valsum, (size_t)rows)) != APB_OK) return rc;
+    if ((rc = launch_slot_major_signs(d.sign, d.perm, d.Np, d.Kw, Kw2, d.signT, s)) != APB_OK) return rc;
+    if ((rc = launch_slot_major_signs(d.sign, nullptr, N, d.Kw, Kw2, d.signC, s)) != APB_OK) return rc;
     if ((rc = launch_row_valsum(d.row_ptr, d.val, N, rows, d.rows_valsum, s)) != APB_OK) return rc;
     if ((rc = launch_slot_tables(d.perm, d.row_ptr, d.col_idx, d.rows_valsum, d.Np, d.nchunks, d.chunk_ptr, d.slot_valsum,
                                  s)) != APB_OK)
         return rc;
-    if (K <= kRowsMaxK && (rc = build_rows_layer(d, s)) != APB_OK) return rc;
-    if (K <= kRowsMaxK && !columns_kernel_possible(N, K, nnz)) return APB_OK;   // (it waited: the staging vectors may go)
-
-    // Tile runs for the columns-in-lanes kernel: built on the host from the CSR just written.
-    std::vector<int32_t> hcol((size_t)nnz);
-    std::vector<float> hval((size_t)nnz);
-    if (nnz > 0) {
-        APB_HIP(hipMemcpyAsync(hcol.data(), d.col_idx, (size_t)nnz * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        APB_HIP(hipMemcpyAsync(hval.data(), d.val, (size_t)nnz * sizeof(float), hipMemcpyDeviceToHost, s));
-    }
-    APB_HIP(hipStreamSynchronize(s));
-    std::vector<int32_t> hseg;
-    std::vector<uint32_t> hent;
-    build_tile_runs(hperm, hrow_ptr, hcol, hval, d.nchunks, hseg, hent);
-    if ((rc = dev_alloc(&d.seg_ptr, hseg.size())) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.ent, hent.size())) != APB_OK) return rc;
-    APB_HIP(hipMemcpyAsync(d.seg_ptr, hseg.data(), hseg.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    if (!hent.empty())
-        APB_HIP(hipMemcpyAsync(d.ent, hent.data(), hent.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+    // Tile runs for the columns-in-lanes kernel are built on the host from the CSR just written, which comes over (the
+    // columns and the values behind them) while the digit steps are built.
+    const bool tile_runs = !digits || columns_kernel_possible(N, K, nnz);
+    const size_t val_at = reinterpret_cast<uint8_t*>(d.val) - reinterpret_cast<uint8_t*>(d.col_idx);
+    std::vector<uint8_t> hcsr(tile_runs ? val_at + (size_t)nnz * sizeof(float) : 0);
+    if (tile_runs && nnz > 0) APB_HIP(hipMemcpyAsync(hcsr.data(), d.col_idx, hcsr.size(), hipMemcpyDeviceToHost, s));
+    if (digits && (rc = build_rows_layer(d, found, s)) != APB_OK) return rc;
+    if (!tile_runs) return APB_OK;                     // (it waited for the stream: the staging vectors may go)
+    if (!digits) APB_HIP(hipStreamSynchronize(s));
+    std::vector<uint32_t> runs;                        // seg_ptr, then the entries from a multiple of 64 words on
+    size_t ent_at = 0;
+    build_tile_runs(hperm, hrow_ptr, reinterpret_cast<const int32_t*>(hcsr.data()), reinterpret_cast<const float*>(hcsr.data() + val_at), nnz,
+                    d.nchunks, runs, ent_at);
+    uint32_t* base = nullptr;
+    if ((rc = dev_alloc(&base, runs.size())) != APB_OK) return rc;
+    d.blocks[3] = base;
+    d.seg_ptr = reinterpret_cast<int32_t*>(base);
+    d.ent = base + ent_at;
+    APB_HIP(hipMemcpyAsync(base, runs.data(), runs.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
     APB_HIP(hipStreamSynchronize(s));                 // host staging vectors go out of scope after this
     return APB_OK;
 }

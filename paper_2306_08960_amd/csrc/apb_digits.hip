@@ -256,14 +256,6 @@ size_t digit_steps_lds(int Kw, int most_steps) { return 4u * kCodeWords + 4u * 3
 // (18432 columns, all of them on the list: 49 KB)
 static_assert(4u * kCodeWords + 16u * (kRowsMaxK / 32) + 2u * kRowsMaxK <= 64 * 1024, "the LDS that a launch gets without asking");
 
-template <typename T>
-struct Scratch {                                                 // device memory of one call
-    T* p = nullptr;
-    ~Scratch() {
-        if (p) (void)hipFree(p);
-    }
-};
-
 }  // namespace
 
 int launch_row_valsum(const int32_t* row_ptr, const float* val, int N, int rows, double* valsum, hipStream_t s) {
@@ -273,65 +265,64 @@ int launch_row_valsum(const int32_t* row_ptr, const float* val, int N, int rows,
     return APB_OK;
 }
 
-int build_rows_layer(LayerDev& d, hipStream_t s) {
+size_t digit_scratch_words(int N) { return 2 + (size_t)4 * ((N + 31) / 32) * kMaxWindows; }
+
+int build_rows_layer(LayerDev& d, int32_t* found, hipStream_t s) {
     const int tiles = 2 * ((d.N + 31) / 32), quads = 2 * tiles;
-    int rc;
-    d.rows_ksteps = (d.Kw + 3) / 4;
     const long long words = (long long)tiles * d.rows_ksteps * 64;
-    if ((rc = dev_alloc(&d.rows_sign, (size_t)words)) != APB_OK) return rc;
     hipLaunchKernelGGL(k_rows_sign, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, d.sign, d.N, d.Kw, d.rows_ksteps, words,
                        d.rows_sign);
     APB_HIP(hipGetLastError());
 
-    // range of the residuals' bits, and from it the lengths of the lists
-    Scratch<int32_t> found, step_first;                          // [0], [1]: the range; then [quads][kMaxWindows] lengths
-    std::vector<int32_t> h((size_t)quads * kMaxWindows + 2);
+    // range of the residuals' bits, and from it the lengths of the lists: [0], [1] the range, then [quads][kMaxWindows]
+    std::vector<int32_t> h(digit_scratch_words(d.N));
     h[0] = INT_MAX;
     h[1] = INT_MIN;
-    if ((rc = dev_alloc(&found.p, h.size())) != APB_OK) return rc;
-    APB_HIP(hipMemcpyAsync(found.p, h.data(), 2 * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    APB_HIP(hipMemcpyAsync(found, h.data(), 2 * sizeof(int32_t), hipMemcpyHostToDevice, s));
     if (d.nnz > 0) {
         const long long blocks = (d.nnz + 4 * kBlock - 1) / (4 * kBlock);
-        hipLaunchKernelGGL(k_residual_range, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(kBlock), 0, s, d.val, d.nnz, found.p);
+        hipLaunchKernelGGL(k_residual_range, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(kBlock), 0, s, d.val, d.nnz, found);
         APB_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_longest_lists, dim3((unsigned)quads), dim3(4 * kWave), 4u * (4 * d.Kw + 4), s, d.row_ptr, d.col_idx, d.val, d.N, d.Kw,
-                       found.p, found.p + 2);
+                       found, found + 2);
     APB_HIP(hipGetLastError());
-    APB_HIP(hipMemcpyAsync(h.data(), found.p, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    APB_HIP(hipMemcpyAsync(h.data(), found, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     APB_HIP(hipStreamSynchronize(s));
 
     const int W = windows_of(h[0], h[1]);
     d.rows_windows = W;
     d.rows_unit_log2 = h[0] == INT_MAX ? 0 : h[0];
-    std::vector<int32_t> first((size_t)tiles + 1), quad_first((size_t)quads * W + 1);
-    std::vector<uint8_t> count((size_t)quads * W);
+    // One upload: first step of each tile, first step of each quad and window, and (bytes) the steps of a pair there.
+    const size_t lists = (size_t)quads * W, at_lists = (size_t)tiles + 1, at_count = at_lists + lists + 1;
+    std::vector<int32_t> up(at_count + (lists + 3) / 4, 0);
+    uint8_t* count = reinterpret_cast<uint8_t*>(up.data() + at_count);
     long long steps = 0;
     int most = 1;
     for (int quad = 0; quad < quads; ++quad) {
-        if (quad % 2 == 0) first[quad / 2] = (int32_t)steps;
+        if (quad % 2 == 0) up[quad / 2] = (int32_t)steps;
         for (int w = 0; w < W; ++w) {
             const int S = digit_steps_of(h[2 + (size_t)quad * kMaxWindows + w]);
             count[(size_t)quad * W + w] = (uint8_t)S;
-            quad_first[(size_t)quad * W + w] = (int32_t)steps;
+            up[at_lists + (size_t)quad * W + w] = (int32_t)steps;
             steps += 4 * S;
             most = S > most ? S : most;
         }
     }
     if (steps > INT_MAX - kStepPad) return APB_ERR_NOMEM;        // (the steps alone would take 3 TB)
-    first[tiles] = quad_first.back() = (int32_t)steps;
+    up[tiles] = up[at_count - 1] = (int32_t)steps;
     d.rows_steps = steps;
-    if ((rc = dev_alloc(&d.rows_first, first.size())) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.rows_count, count.size() + 16)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&d.rows_step, (size_t)(steps + kStepPad) * kStepBytes)) != APB_OK) return rc;
-    if ((rc = dev_alloc(&step_first.p, quad_first.size())) != APB_OK) return rc;
-    APB_HIP(hipMemcpyAsync(d.rows_first, first.data(), first.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    APB_HIP(hipMemcpyAsync(d.rows_count, count.data(), count.size(), hipMemcpyHostToDevice, s));
-    APB_HIP(hipMemcpyAsync(step_first.p, quad_first.data(), quad_first.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    DeviceArrays arrays;
+    arrays.add(&d.rows_first, up.size() + 4);                    // (counts are read four at a time)
+    arrays.add(&d.rows_step, (size_t)(steps + kStepPad) * kStepBytes);
+    const int rc = arrays.alloc(&d.blocks[2]);
+    if (rc != APB_OK) return rc;
+    d.rows_count = reinterpret_cast<uint8_t*>(d.rows_first + at_count);
+    APB_HIP(hipMemcpyAsync(d.rows_first, up.data(), up.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_digit_steps, dim3((unsigned)(4 * quads + 1)), dim3(kWave), digit_steps_lds(d.Kw, most), s, d.row_ptr, d.col_idx, d.val,
-                       d.N, d.Kw, d.rows_unit_log2, W, d.K <= kRowsByteK ? 8 : 1, step_first.p, d.rows_step);
+                       d.N, d.Kw, d.rows_unit_log2, W, d.K <= kRowsByteK ? 8 : 1, d.rows_first + at_lists, d.rows_step);
     APB_HIP(hipGetLastError());
-    APB_HIP(hipStreamSynchronize(s));                            // (the staging vectors and the scratch end here)
+    APB_HIP(hipStreamSynchronize(s));                            // (the staging vectors end here)
     return APB_OK;
 }
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "apb.h"
 
 namespace apb {
@@ -19,6 +21,8 @@ constexpr int kEntValScaleLog2 = 895;
 constexpr int kEntBlockWords = 24;   // one block of 8 residual entries: 8 key words + 8 float64
 
 struct LayerDev {
+    void* blocks[4] = {};        // the allocations that everything below lies in: what N and K give the size of, the
+                                 // CSR, the digit steps, the tile runs
     int N = 0, K = 0, Kw = 0;    // Kw = ceil(K/32)
     int Np = 0;                  // launch slots: N rounded up to a multiple of kRowTile * waves
     int waves = 2;               // waves per workgroup of the forward kernel (2, 4 or 8)
@@ -127,6 +131,31 @@ int dev_alloc(T** p, size_t count) {
     return APB_OK;
 }
 
+// Several arrays in one allocation: `add` each, then `alloc` sets all the pointers.  (An allocation and its release cost
+// about as much as one of the kernels that compress a layer.)
+struct DeviceArrays {
+    struct Piece {
+        void** p;
+        size_t at;
+    };
+    std::vector<Piece> pieces;
+    size_t bytes = 0;
+
+    template <typename T>
+    void add(T** p, size_t count) {
+        pieces.push_back({reinterpret_cast<void**>(p), bytes});
+        bytes += (count * sizeof(T) + 255) / 256 * 256;
+    }
+    int alloc(void** block) {
+        uint8_t* base = nullptr;
+        const int rc = dev_alloc(&base, bytes);
+        if (rc != APB_OK) return rc;
+        *block = base;
+        for (const Piece& q : pieces) *q.p = base + q.at;
+        return APB_OK;
+    }
+};
+
 // ---- kernel launchers (each returns an apb_status) ------------------------------------------
 
 // compress
@@ -141,8 +170,10 @@ int launch_slot_major_signs(const uint32_t* sign, const int32_t* perm, int Np, i
 int launch_slot_tables(const int32_t* perm, const int32_t* row_ptr, const int32_t* col_idx, const double* row_valsum, int Np,
                        int nchunks, int32_t* chunk_ptr, double* slot_valsum, hipStream_t s);
 int launch_row_valsum(const int32_t* row_ptr, const float* val, int N, int rows, double* valsum, hipStream_t s);
-// everything of LayerDev that begins with rows_ but for rows_valsum, from the sign words and the CSR; waits for the stream
-int build_rows_layer(LayerDev& d, hipStream_t s);
+// The operands of the matrix-core forward kernel: the sign words in its lanes' order, and the digit steps, from the sign
+// words and the CSR.  `found` is scratch of digit_scratch_words(N) words.  Waits for the stream.
+size_t digit_scratch_words(int N);
+int build_rows_layer(LayerDev& d, int32_t* found, hipStream_t s);
 
 // activations.  colsum == nullptr: the planes only (for a consumer that adds the code sums up from the words itself)
 int launch_quantize(const float* X, int K, int M, int bits, float inv_step, uint32_t* planes, int32_t* colsum,
