@@ -30,7 +30,9 @@ SHAPES = [(1, 1, 1), (5, 33, 3), (16, 64, 64), (30, 100, 65), (33, 257, 130), (6
           # more than 512 strips of columns (several rounds of workgroups on the chip): an odd number of strips,
           # ragged M and K, 8-, 4- and 2-wave row groups, and values of K whose strip takes 15 to 39 KB of LDS
           (128, 1152, 32900), (64, 300, 40000), (20, 97, 33333), (128, 1500, 32800), (64, 1800, 32770),
-          (128, 2400, 32800)]
+          (128, 2400, 32800),
+          # 65 to 128 rows: one kernel up to K = 512 whatever M
+          (128, 512, 16385), (66, 40, 3000), (90, 513, 16385)]
 
 
 @pytest.mark.parametrize("bits", [1, 2])
