@@ -122,6 +122,10 @@ inline RowsShape pick_rows_shape(const RowsProblem& q) {
         // (A column group alone may have more workgroups than that: the doubling ends at all tiles.)
         h = RowsShape{1, 1, 1, 2, 2};
         while (h.chunk < tiles && ct16 * ((tiles + h.chunk - 1) / h.chunk) > 4 * kComputeUnits) h.chunk *= 2;
+        // A packed output whose rows sit in several workgroups needs a launch that clears the column sums first (2 us);
+        // up to 256 rows of not too long a K are done sooner by one (192 x 4608, 256 columns: 12.1 us and 11.5; 256 x 4608:
+        // 12.1 and 13.1; 256 x 2304 and less: 12.1 and 10.0).
+        if (q.packed_out && tiles <= 16 && tiles * ksteps <= 450) h.chunk = tiles;
         h.waves = std::min(8, h.chunk);
         return h;
     }
