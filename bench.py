@@ -34,7 +34,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0                  # MI355X HBM3E, published
-MFMA_FP4_PEAK_TFLOPS = 10100.0         # dense FP4 MFMA, published
+MFMA_FP4_PEAK_TFLOPS = 10100.0         # dense FP4 and FP6 MFMA, published
 FP64_VECTOR_PEAK_TFLOPS = 78.6         # 256 CUs x 64 lanes x 2.4 GHz x 2 (fused multiply-add)
 VALU_LANE_OPS_PER_S = 256 * 64 * 2.4e9 # 39.3e12 32-bit vector lane-ops/s: the bit-op roof of a popcount formulation
 
@@ -132,26 +132,36 @@ def measured_traffic(workload, kernel_key):
     return None
 
 
-def forward_floors(N, K, M, bits, nnz):
-    """Seconds the forward kernel cannot go below: the bytes it must move (sign words, bit-planes, residual
-    entries, Y) at the HBM peak, the binary product at the FP4 matrix-core peak, the residual multiply-adds
-    at the float64 vector peak; and the yardstick the benchmark spec names, the vector-ALU bit-op time of
-    the popcount formulation (per weight word, plane and column one logic op + one accumulating popcount,
-    per residual and column one multiply-add)."""
-    Kw, Mp = (K + 31) // 32, 64 * ((M + 63) // 64)
-    fwd_bytes = 4.0 * N * Kw + 4.0 * bits * Kw * Mp + 4.0 * Mp + 12.0 * nnz + 4.0 * N * M
-    return {"hbm": fwd_bytes / (HBM_PEAK_GBS * 1e9), "mfma_fp4": 2.0 * N * K * M / (MFMA_FP4_PEAK_TFLOPS * 1e12),
-            "fp64_vector": 2.0 * nnz * M / (FP64_VECTOR_PEAK_TFLOPS * 1e12),
-            "valu_bitop_yardstick": (2.0 * bits * N * Kw * M + float(nnz) * M) / VALU_LANE_OPS_PER_S}, fwd_bytes
+def forward_floors(N, K, M, bits, nnz, kernel, fwd_bytes):
+    """Seconds the forward kernel cannot go below: the bytes it must move at the HBM peak, the binary product at the FP4
+    matrix-core peak, the residual part on the unit that computes it -- six base-32 digits per residual, FP6, on the
+    matrix cores (k_forward_rows; also where the kernel is not named, this being the lower floor), or a float64 multiply-add
+    on the vector ALU (the columns-in-lanes kernels); and the
+    yardstick the benchmark spec names, the vector-ALU bit-op time of the popcount formulation (per weight word, plane
+    and column one logic op + one accumulating popcount, per residual and column one multiply-add)."""
+    Kw = (K + 31) // 32
+    fl = {"hbm": fwd_bytes / (HBM_PEAK_GBS * 1e9), "mfma_fp4": 2.0 * N * K * M / (MFMA_FP4_PEAK_TFLOPS * 1e12),
+          "valu_bitop_yardstick": (2.0 * bits * N * Kw * M + float(nnz) * M) / VALU_LANE_OPS_PER_S}
+    if not kernel.startswith(("k_sparse_epilogue", "k_forward_ksplit")):
+        fl["mfma_fp6_digits"] = 12.0 * nnz * M / (MFMA_FP4_PEAK_TFLOPS * 1e12)
+    else:
+        fl["fp64_vector"] = 2.0 * nnz * M / (FP64_VECTOR_PEAK_TFLOPS * 1e12)
+    return fl
 
 
-def forward_roofline(N, K, M, bits, nnz, ms, kernel, traffic=None):
-    fl, fwd_bytes = forward_floors(N, K, M, bits, nnz)
+def forward_roofline(N, K, M, bits, nnz, ms, kernel, traffic=None, fwd_bytes=None):
+    """fwd_bytes: what must move; by default sign words, bit-planes, residual entries, Y."""
+    if fwd_bytes is None:
+        Kw, Mp = (K + 31) // 32, 64 * ((M + 63) // 64)
+        fwd_bytes = 4.0 * N * Kw + 4.0 * bits * Kw * Mp + 4.0 * Mp + 12.0 * nnz + 4.0 * N * M
+    fl = forward_floors(N, K, M, bits, nnz, kernel, fwd_bytes)
     t = ms * 1e-3
-    if fl["hbm"] >= max(fl["mfma_fp4"], fl["fp64_vector"]):
+    mfma = fl["mfma_fp4"] + fl.get("mfma_fp6_digits", 0.0)      # the same matrix cores, one after the other
+    f64 = fl.get("fp64_vector", 0.0)
+    if fl["hbm"] >= max(mfma, f64):
         roof = {"bound": "hbm", "achieved": fwd_bytes / t / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
-    elif fl["mfma_fp4"] >= fl["fp64_vector"]:
-        roof = {"bound": "mfma", "achieved": 2.0 * N * K * M / t / 1e12, "peak": MFMA_FP4_PEAK_TFLOPS, "unit": "TFLOP/s"}
+    elif mfma >= f64:
+        roof = {"bound": "mfma", "achieved": mfma * MFMA_FP4_PEAK_TFLOPS / t, "peak": MFMA_FP4_PEAK_TFLOPS, "unit": "TFLOP/s"}
     else:
         roof = {"bound": "alu", "achieved": 2.0 * nnz * M / t / 1e12, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s"}
     roof = {"kernel": kernel} | roof
@@ -232,11 +242,12 @@ def run_workload(name, steps, warmup, calibration_copy=False):
     roof_quant["frac"] = roof_quant["achieved"] / roof_quant["peak"]
     roof_fwd = forward_roofline(N, K, M, bits, nnz, ms_fwd, b.apb_forward_kernel_name(layer, M, bits),
                                 measured_traffic(name, "forward"))
-    # Layers of at most 128 rows run the step as ONE kernel (quantize into LDS + forward): it reads X and the
-    # layer and writes Y, nothing else, so its floor is those bytes at the HBM peak.
+    # Layers of at most 128 rows, and small X, run the step as ONE kernel (quantize into LDS + forward): it reads X and
+    # the layer and writes Y, nothing else, so its floor is those bytes at the HBM peak.
     one_bytes = 4.0 * K * M + 4.0 * N * M + 4.0 * N * Kw + 12.0 * nnz
-    roof_one = {"kernel": b.apb_forward_kernel_name(layer, M, bits).replace("false>", "true>") +
-                          " (float input: quantize + forward in one kernel)", "bound": "hbm",
+    fwd_name = b.apb_forward_kernel_name(layer, M, bits)
+    roof_one = {"kernel": (re.sub(r"<(\d), 0,", r"<\1, 2,", fwd_name) if fwd_name.startswith("k_forward_rows") else
+                           fwd_name.replace("false>", "true>")) + " (float input: quantize + forward in one kernel)", "bound": "hbm",
                 "achieved": one_bytes / (ms_step_graph * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "traffic": measured_traffic(name, "one_kernel_step"),
                 "algorithmic_bytes": one_bytes, "ms": ms_step_graph}
@@ -350,22 +361,9 @@ def run_chain(name, steps, warmup):
     ops = 2.0 * N * K * M + 2.0 * nnz * M
     Kw, Mp, Nw = (K + 31) // 32, 64 * ((M + 63) // 64), (N + 31) // 32
     out_bytes = 4.0 * (bits_out * Nw + 1) * Mp
-    # sign words, bit-planes, residual entries in; the packed output is stored once (layers of at most 128 rows)
-    # or zero-filled, then read-modify-written
-    fwd_bytes = 4.0 * N * Kw + 4.0 * bits * Kw * Mp + 4.0 * Mp + 12.0 * nnz + (1.0 if N <= 128 else 3.0) * out_bytes
-    t_hbm = fwd_bytes / (HBM_PEAK_GBS * 1e9)
-    t_mfma = 2.0 * N * K * M / (MFMA_FP4_PEAK_TFLOPS * 1e12)
-    t_f64 = 2.0 * nnz * M / (FP64_VECTOR_PEAK_TFLOPS * 1e12)
-    t = ms_call * 1e-3
-    if t_hbm >= max(t_mfma, t_f64):
-        roof = {"bound": "hbm", "achieved": fwd_bytes / t / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
-    elif t_mfma >= t_f64:
-        roof = {"bound": "mfma", "achieved": 2.0 * N * K * M / t / 1e12, "peak": MFMA_FP4_PEAK_TFLOPS, "unit": "TFLOP/s"}
-    else:
-        roof = {"bound": "alu", "achieved": 2.0 * nnz * M / t / 1e12, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s"}
-    roof = {"kernel": "forward kernel with the packed-output epilogue (+ zero fill)"} | roof
-    roof |= {"frac": roof["achieved"] / roof["peak"], "traffic": None, "ms": ms_call,
-             "floor_us": {"hbm": t_hbm * 1e6, "mfma_fp4": t_mfma * 1e6, "fp64_vector": t_f64 * 1e6}}
+    # sign words, bit-planes, residual entries in; the packed output out
+    fwd_bytes = 4.0 * N * Kw + 4.0 * bits * Kw * Mp + 4.0 * Mp + 12.0 * nnz + out_bytes
+    roof = forward_roofline(N, K, M, bits, nnz, ms_call, "forward kernel, packed-output epilogue (+ a fill of the column sums)", None, fwd_bytes)
     res = {"workload": name, "N": N, "K": K, "M": M, "act_bits": bits, "nnz": int(nnz), "ms_per_step": ms_chain,
            "gops_step": ops / (ms_chain * 1e-3) / 1e9, "ms_forward_plus_quantize": ms_two, "gops_forward_plus_quantize": ops / (ms_two * 1e-3) / 1e9,
            "same_packed_output": same, "words_differing": differing, "roofline": roof, "bits_out": bits_out, "step_out": step_out}
@@ -431,27 +429,15 @@ def run_conv_chain(name, steps, warmup):
     Kw, Mp, Cw, Nw = (K + 31) // 32, 64 * ((M + 63) // 64), C // 32, (N + 31) // 32
     out_bytes = 4.0 * (bits_out * Nw + 1) * Mp
     # sign words, the packed map (read once from HBM; its nine shifted views hit in cache), residual entries;
-    # the packed output is stored once (layers of at most 128 rows) or zero-filled, then read-modify-written
-    fwd_bytes = 4.0 * N * Kw + 4.0 * (bits * Cw + 1) * Mp + 12.0 * nnz + (1.0 if N <= 128 else 3.0) * out_bytes
-    t_hbm = fwd_bytes / (HBM_PEAK_GBS * 1e9)
-    t_mfma = 2.0 * N * K * M / (MFMA_FP4_PEAK_TFLOPS * 1e12)
-    t_f64 = 2.0 * nnz * M / (FP64_VECTOR_PEAK_TFLOPS * 1e12)
-    t = ms_call * 1e-3
-    if t_hbm >= max(t_mfma, t_f64):
-        roof = {"bound": "hbm", "achieved": fwd_bytes / t / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
-    elif t_mfma >= t_f64:
-        roof = {"bound": "mfma", "achieved": 2.0 * N * K * M / t / 1e12, "peak": MFMA_FP4_PEAK_TFLOPS, "unit": "TFLOP/s"}
-    else:
-        roof = {"bound": "alu", "achieved": 2.0 * nnz * M / t / 1e12, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s"}
-    roof = {"kernel": "forward kernel, implicit im2col + packed-output epilogue (+ fill of the column sums)"} | roof
-    roof |= {"frac": roof["achieved"] / roof["peak"], "traffic": None, "ms": ms_call,
-             "floor_us": {"hbm": t_hbm * 1e6, "mfma_fp4": t_mfma * 1e6, "fp64_vector": t_f64 * 1e6}}
-    t_valu = (2.0 * bits * N * Kw * M + float(nnz) * M) / VALU_LANE_OPS_PER_S
+    # the packed output
+    fwd_bytes = 4.0 * N * Kw + 4.0 * (bits * Cw + 1) * Mp + 12.0 * nnz + out_bytes
+    roof = forward_roofline(N, K, M, bits, nnz, ms_call, "forward kernel, implicit im2col, packed-output epilogue (+ a fill of the column sums)", None,
+                            fwd_bytes)
     res = {"workload": name, "N": N, "C": C, "B": B, "H": H, "W": W_, "act_bits": bits, "nnz": int(nnz),
            "ms_per_step": ms_chain, "gops_step": ops / (ms_chain * 1e-3) / 1e9,
            "ms_step_graph": ms_call, "ms_conv_float_output": ms_float, "ms_explicit_im2col_quantize_plus_forward": ms_explicit,
            "implicit_equals_explicit_bitwise": same, "roofline": roof, "bits_out": bits_out, "step_out": step_out,
-           "frac_of_valu_bitop_roof": t_valu / t}
+           "frac_of_valu_bitop_roof": roof["frac_of_valu_bitop_yardstick"]}
     layer.free()
     return res, cfg
 
@@ -677,7 +663,7 @@ def main():
             "metric": "APB 3x3 conv layer GOPS, chained (packed feature map in, packed feature map out)",
             "value": res["gops_step"], "unit": "GOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": res["ms_per_step"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-            "dtype": "fp4 (exact 0/1 and 2-bit codes) on MFMA + f64 accumulate, packed codes in/out", "data": "synthetic",
+            "dtype": "fp4 codes and fp6 digits, exact, on MFMA + one f64 rounding, packed codes in/out", "data": "synthetic",
             "config": {"workload": f"{cfg.name}: {cfg.note}", "N": res["N"], "C": res["C"], "B": res["B"], "H": res["H"],
                        "W": res["W"], "act_bits": cfg.bits, "outlier_rate": cfg.rho, "nnz": res["nnz"],
                        "bits_out": res["bits_out"], "step_out": res["step_out"],
@@ -696,7 +682,7 @@ def main():
             "metric": "APB layer forward GOPS, chained (packed activations in, packed activations out)",
             "value": res["gops_step"], "unit": "GOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": res["ms_per_step"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-            "dtype": "fp4 (exact 0/1 and 2-bit codes) on MFMA + f64 accumulate, packed codes in/out", "data": "synthetic",
+            "dtype": "fp4 codes and fp6 digits, exact, on MFMA + one f64 rounding, packed codes in/out", "data": "synthetic",
             "config": {"workload": f"{cfg.name}: {cfg.note}", "N": cfg.N, "K": cfg.K, "M": cfg.M, "act_bits": cfg.bits,
                        "outlier_rate": cfg.rho, "nnz": res["nnz"], "bits_out": res["bits_out"], "step_out": res["step_out"],
                        "step": "apb_forward_requant, packed input resident in HBM"},
@@ -720,11 +706,11 @@ def main():
         "metric": "APB layer forward GOPS (binary+sparse) and % of MI355X roofline",
         "value": res["gops_step"], "unit": "GOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": res["ms_per_step"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "fp4 (exact 0/1 and 2-bit codes) on MFMA + f64 accumulate (f32 in/out)", "data": "synthetic",
+        "dtype": "fp4 codes and fp6 digits, exact, on MFMA + one f64 rounding (f32 in/out)", "data": "synthetic",
         "config": {"workload": f"{cfg.name}: {cfg.note}", "N": cfg.N, "K": cfg.K, "M": cfg.M,
                    "act_bits": cfg.bits, "outlier_rate": cfg.rho, "nnz": res["nnz"],
                    "step": "apb_quantize_forward (= apb_quantize_acts + apb_forward; one kernel for layers of at most "
-                           "128 rows), inputs resident in HBM", "one_kernel_step": res["one_kernel_step"]},
+                           "128 rows and for small inputs), inputs resident in HBM", "one_kernel_step": res["one_kernel_step"]},
         "ms_step_graph": res["ms_step_graph"], "gops_step_graph": res["gops_step_graph"],
         "ms_quantize": res["ms_quantize"], "ms_quantize_in_step": res["ms_quantize_in_step"],
         "ms_forward": res["ms_forward"], "ms_forward_in_step": res["ms_forward_in_step"], "gops_forward_only": res["gops_forward"],
@@ -860,7 +846,7 @@ def routine_resnet18(args):
         tf = graph_ms(lambda: b.apb_forward(apb, p2, M, 2, float(step), Y=Y))
         tq = graph_ms(lambda: b.apb_quantize_acts(Xd, 2, float(step), packed=p2))
         ops = 2.0 * N * K * M
-        roof = forward_roofline(N, K, M, 2, nnz, tf, "the forward kernel")
+        roof = forward_roofline(N, K, M, 2, nnz, tf, b.apb_forward_kernel_name(apb, M, 2))
         rows.append({"layer": lname, "N": N, "K": K, "M": M, "nnz": int(nnz), "us_1_1": t11 * 1e3, "us_1_2": t12 * 1e3,
                      "us_2_2": t22 * 1e3, "us_apb_forward": tf * 1e3, "us_quantize": tq * 1e3,
                      "tops_1_1": ops / t11 / 1e9, "tops_1_2": ops / t12 / 1e9, "tops_2_2": ops / t22 / 1e9,

@@ -15,7 +15,8 @@
  * spreads the bits it owns into 4-bit operand slots; the algebra is that of the
  * paper's and/xor + popcount forms, Eqs. 16, 18, 19, which are kept as the
  * *_popcount entry points for comparison).  The sparse product reads the same
- * packed activations.
+ * packed activations; for most layers it runs on the matrix cores as well, the
+ * residuals cut into base-32 digits whose sums are exact.
  *
  * Shapes and names: W is N x K row-major (N output channels, K = C_in*kh*kw),
  * X is K x M row-major (column m = one im2col patch), Y is N x M row-major.
@@ -67,7 +68,9 @@ typedef enum apb_status {
 } apb_status;
 
 /* Opaque compressed layer.  Holds, in device memory: the sign words, the CSR of
- * residuals, per-row sign sums and a launch-order row permutation. */
+ * residuals, per-row sums, a launch-order row permutation, and the residuals as the
+ * forward kernels read them (digit steps: 1408 bytes for up to 128 columns at which one
+ * of two rows has a residual, one step at least). */
 typedef struct apb_layer apb_layer;
 
 /* Sec. III Eq. 1 (sign(0) = +), Eq. 3 (partition), Eqs. 11-12 (A^bin, A^full).
@@ -122,8 +125,9 @@ int apb_quantize_acts(const float* X, int K, int M, int bits, float step, void* 
 /* Sec. III Eq. 13 with the scalar multipliers of Sec. IV:
  *      Y[n,m] = alpha*step * D[n,m] + sum_{j in row n} val_j * step * c[col_j, m]
  * where c is the integer activation value (+-1 or p) and D = sum_k sign(W[n,k]) * c[k,m]
- * is computed exactly in integers from the packed words.  The sparse sum and the
- * combination are accumulated in float64 and rounded once to float.
+ * is computed exactly in integers from the packed words.  The sparse sum is exact up to one
+ * rounding to float64 (layers that run with the columns in the lanes: accumulated in float64);
+ * it is combined with D in float64 and rounded once to float.
  *   packed  DEVICE buffer written by apb_quantize_acts with the SAME K (the layer's), M, bits.
  *   Y       DEVICE, N*M floats row-major, fully overwritten.
  * Asynchronous on `stream`. */
@@ -135,10 +139,9 @@ const char* apb_forward_kernel_name(const apb_layer* layer, int M, int bits);
 
 /* apb_quantize_acts followed by apb_forward as ONE call, with the same Y bit for bit.  For layers of at
  * most 128 rows (one workgroup then holds every row, so no strip of X is quantized twice) whose K fits
- * the on-chip memory, a single kernel reads X, keeps the packed codes of its 64 columns on chip and
- * writes Y: the packed activations never travel to HBM and the memory-bound quantize phase of one
- * workgroup overlaps the arithmetic of the others.  Other layers run the two kernels one after the
- * other through `packed`.
+ * the on-chip memory and whose columns fill the chip, and for small X (K * M <= 65536), a single kernel
+ * reads X, keeps the codes of its columns on chip and writes Y: the packed activations never travel to HBM.
+ * Other layers run the two kernels one after the other through `packed`.
  *   X       DEVICE, K*M floats row-major, read-only.
  *   packed  DEVICE, apb_acts_bytes(K, M, bits) bytes of scratch; contents unspecified afterwards.
  *   Y       DEVICE, N*M floats, fully overwritten.

@@ -30,8 +30,10 @@ HIPCC_FLAGS = [
     "-Wall", "-Wextra", "-Wno-unused-parameter",
 ]
 
-# Per source.  apb_rows.hip: all its branches are wave-uniform; structurizing them anyway makes the register allocator
-# keep two versions of the wave's state across every one of them (60 spilled registers instead of none).
+# Per source.  apb_rows.hip: a switch of the compiler's control-flow structurizer that leaves regions alone whose branches it
+# has found uniform (the loops over items, quads and steps, the switch over step counts); divergent ones (predicates of the
+# epilogue, loops strided over threads) are structurized as ever.  Without it the register allocator keeps two versions
+# of a wave's state across every uniform branch (60 spilled registers instead of none).
 EXTRA_FLAGS = {"apb_rows.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
 
 

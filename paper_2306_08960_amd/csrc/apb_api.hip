@@ -1,4 +1,4 @@
-// Host side of the C ABI: argument checks, layer ownership, launch-order row binning.
+// Host side of the C ABI: argument checks, layer ownership, launch-order row binning, tile runs.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -46,7 +46,7 @@ std::vector<int32_t> balanced_slots(const std::vector<int32_t>& counts, int Np) 
     return perm;
 }
 
-// Regroup the CSR for the sparse kernel: for every tile of kRowTile launch slots and every chunk of
+// Regroup the CSR for the columns-in-lanes kernel: for every tile of kRowTile launch slots and every chunk of
 // kChunkK columns one flat run of entries, sorted by (row in tile, column) and padded to whole
 // blocks of 8.  A block is 24 words: 8 keys (2*row | column_in_chunk << 8), then the 8 residuals as
 // float64 times 2^kEntValScaleLog2; padding entries have key 0 and value 0.  seg_ptr, which counts blocks, lies at the

@@ -15,7 +15,7 @@ constexpr int kRowTile = 16;     // weight rows one wave keeps in registers in t
 constexpr int kChunkWords = 8;   // K is walked in chunks of 8 words = 256 weights (one LDS code table each)
 constexpr int kChunkK = 32 * kChunkWords;
 constexpr int kMaxWavesPerBlock = 8;
-// ent_val holds residual * 2^895: finite for every float, and large enough that the sparse kernel's
+// ent_val holds residual * 2^895: finite for every float, and large enough that the columns-in-lanes kernel's
 // table codes (code * 2^-1009, see apb_sparse.hip) give products far from underflow.
 constexpr int kEntValScaleLog2 = 895;
 constexpr int kEntBlockWords = 24;   // one block of 8 residual entries: 8 key words + 8 float64

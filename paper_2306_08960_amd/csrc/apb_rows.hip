@@ -3,13 +3,14 @@
 // with BOTH parts on the matrix cores, exactly.
 //
 // Residual part.  Over the residuals of a row, R is a sum of float32 values times small integers: a sum of
-// integers once the values of the row are written in units of a power of two small enough for all of them (the
-// row's scale).  Those integers are cut into signed base-32 digits, -16 .. 16, which the FP6 format (E2M3) holds
+// integers once the values are written in units of a power of two small enough for all of them (the
+// layer's unit).  Those integers are cut into signed base-32 digits, -16 .. 16, which the FP6 format (E2M3) holds
 // exactly, and the digits are multiplied by the FP4 codes with v_mfma_scale_f32_16x16x128_f8f6f4: every product
 // and every partial sum is an integer far below 2^24, so the float accumulators are exact, and putting the digit
 // sums together gives R without any rounding (one rounding follows in float64, one to float).  Six digits span 30
-// bits; a float has 24, so that covers rows whose magnitudes differ by up to 2^5 -- residuals of a trained layer
-// do by less -- and other layers take several windows of six digits.
+// bits; a float has 24, so that covers layers whose residuals' last bits and largest bits lie up to 2^29 apart
+// (residuals are differences of a weight and alpha, whose last bits are those of the smaller of the two); other
+// layers take several windows of six digits.
 //
 // The matrix instruction multiplies 16 rows by 16 columns over 128 values of k.  The 16 rows are the 6 + 6 digits
 // of TWO rows of the layer (and four idle ones); the 128 values of k are not consecutive ones but those at which
@@ -19,8 +20,7 @@
 // lane names the row it reads, fetches 64 arbitrary rows of the table and hands every lane its column of them --
 // the gather IS the operand load.  128 residuals (of two rows, 16 columns each) thus cost two LDS reads and one
 // matrix instruction of 16 cycles, where the vector ALU needs 16 x 128 / 64 = 32 mask + multiply-add pairs of 9.
-// What bounds the loop is the LDS: a wave's two gathers take 23 cycles of a SIMD's share when the rows of each
-// half wave fall into different banks (k mod 32 all different; 60 cycles where they fall at random), so the order
+// The rows of each half wave of a gather should fall into different banks (k mod 32 all different), so the order
 // of the k of a list -- free -- is chosen when the layer is built.
 //
 // Binary part.  The same table serves as the activation operand, the weight operand is expanded from the sign bits.
@@ -29,12 +29,14 @@
 // tiles of 16 rows x NCW column groups with no further barriers.  Convolutions gather the table from the packed feature
 // map, and the one-kernel step quantizes X into it.  A packed output leaves as whole words (two tiles) or half words.
 //
-// Measured against the kernel this replaces, which had residuals of one row after another in scalar registers and 64
-// columns in the lanes, and summed in float64 (forward alone, both parts): 512 x 4608, 12544 columns, 3 %
-// residuals 87 -> 44.5 us; 4096 x 4096, 256 columns 21.4 -> 14.4; 1000 x 517, 333 columns 9.5 -> 5.5;
-// 256 x 2304 1-bit, 8192 columns 17.7 -> 11.0; chained 256-channel convolution on 14 x 14, 64 images 37 -> 19.5 (its patch
-// matrix no longer goes through memory).  What bounds the largest: the L1 fill of the digit steps (64 bytes a
-// clock and CU), hence items of four column groups there.
+// Measured against a kernel with one row and 16 columns to a lane, which summed the residuals one after another in
+// float64 (forward alone, both parts): 512 x 4608, 12544 columns, 3 % residuals 86 -> 45 us; 4096 x 4096, 256 columns
+// 21.4 -> 14.2; 256 x 2304 1-bit, 8192 columns 17.7 -> 10.6; 128 x 1152, 50176 columns, 1 % in skewed rows 30 -> 23.4.
+// What bounds the largest of these (counters: profiles/forward_C5b_pmc_counters.txt): no unit -- of the compute units in use
+// the vector ALU is busy 44 % of the time, LDS and L1 43 % each (a seventh of the LDS cycles bank conflicts), the matrix
+// cores 28 % -- but that its tables, 152 KB for 64 columns of K = 4608, leave one workgroup of 8 waves to a compute unit
+// and 196 workgroups for 256 of them.  Layers of few residuals per row and many columns are bound by the epilogue and by
+// digit steps that are mostly empty: see columns_kernel_residuals (apb_rows_shape.h).
 #include <algorithm>
 #include <atomic>
 #include <cmath>

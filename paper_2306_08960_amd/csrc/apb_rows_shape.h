@@ -54,9 +54,11 @@ inline bool columns_kernel_possible(int N, int K, long long nnz) {     // for so
 }
 
 // Quantize + forward in one kernel: where one workgroup holds every row of the layer, so that no column of X is
-// quantized twice, and the columns fill the chip (a narrow tail of them would read X with too few waves); and where X is
-// so small (a quarter of a MB: every workgroup's share comes from the L2) or so short (K <= 512, 65 to 128 rows, up to
-// 23000 columns: 11.0 .. 12.5 us against 13.9 .. 15.8 as two kernels) that the launch saved is worth more.
+// quantized twice, and the columns fill the chip (a narrow tail of them would read X with too few waves; 24000 columns:
+// 128 x 1152 26 us against 34 as two kernels, 128 x 2304 48 and 62, 64 x 2304 42 and 59; the line is a careful one: at
+// 16384 columns 128 x 1152 takes 21 and 29); and where X is so small (a quarter of a MB: every workgroup's share comes
+// from the L2) or K so short (K <= 512, 65 to 128 rows, up to 23000 columns: 11.0 .. 12.5 us against 13.9 .. 15.8 as two
+// kernels) that the launch saved is worth more.
 inline bool rows_from_float(int N, int K, int M) {
     if ((long long)K * M <= 65536) return true;
     if (N > kFloatRows || (K + 127) / 128 > 38) return false;
@@ -73,7 +75,8 @@ inline long long rows_lds_bytes(const RowsProblem& q, int groups, int chunk) {
 // How many tiles a workgroup takes (of all, shared evenly) and how many waves work on them.  The time of a launch,
 // in units of a fifth of an item (an item alone on its SIMD takes five): rounds of workgroups on the chip, times the
 // items a wave takes one after another (two waves on a SIMD take 1.5 times as long, four 2.5 times: the matrix cores,
-// the LDS and the L1 fill are shared, latencies overlap) and the table build (which more waves finish sooner).  Next
+// the LDS and the L1 fill are shared, latencies overlap) and the table build (three items' time for one wave, shared).  From
+// four rounds on the last one's emptiness no longer counts, and a split has to gain 3 %.  Next
 // to large tables the rows' own sums may leave room for a share of the tiles only.
 inline void rows_spread(const RowsProblem& q, RowsShape& h, long long cts, int max_waves, int waves_per_cu) {
     const int tiles = rows_tiles(q.N), shares = h.groups / h.ncw;

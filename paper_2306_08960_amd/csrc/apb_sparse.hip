@@ -1,4 +1,5 @@
-// The forward kernel of apb_forward (Sec. III Eqs. 12-13):
+// The forward kernel with the lanes along the columns (Sec. III Eqs. 12-13), for layers of few residuals per row and many
+// outputs, and for K beyond the tables of the matrix-core kernel (apb_rows.hip; columns_kernel_residuals says which):
 //     Y[n,m] = s * ( alpha * D[n,m] + sum_{j in row n} val_j * c[col_j, m] )
 // A workgroup (2, 4 or 8 waves) first computes the binary product of its tile on the matrix cores
 // (binary_tile_to_lds below), starts its float64 row sums at alpha * D, adds the residual part and
