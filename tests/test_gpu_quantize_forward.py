@@ -32,7 +32,9 @@ SHAPES = [(1, 1, 1), (5, 33, 3), (16, 64, 64), (30, 100, 65), (33, 257, 130), (6
           (128, 1152, 32900), (64, 300, 40000), (20, 97, 33333), (128, 1500, 32800), (64, 1800, 32770),
           (128, 2400, 32800),
           # 65 to 128 rows: one kernel up to K = 512 whatever M
-          (128, 512, 16385), (66, 40, 3000), (90, 513, 16385)]
+          (128, 512, 16385), (66, 40, 3000), (90, 513, 16385),
+          # any number of rows: one kernel up to K * M = 65536
+          (300, 256, 256), (300, 256, 257), (2100, 33, 1985)]
 
 
 @pytest.mark.parametrize("bits", [1, 2])

@@ -117,6 +117,29 @@ def test_long_rows_are_summed_exactly(b, K, bits):
     layer.free()
 
 
+@pytest.mark.parametrize("N,K,M", [(100, 700, 90), (64, 300, 2100), (270, 1000, 333)])
+@pytest.mark.parametrize("bits", [1, 2])
+def test_residuals_of_very_different_magnitudes(b, N, K, M, bits):
+    # several windows of digits; in some quads only the lowest or only the highest holds any
+    g = np.random.default_rng(34 + N)
+    W = (g.standard_normal((N, K)) * 0.01).astype(np.float32)
+    for n in range(0, N, 2):
+        cols = g.choice(K, size=n % 50, replace=False)
+        mag = 2.0 ** (g.integers(-1, 18, cols.size) if n % 3 else np.full(cols.size, 17 if n % 4 else 0))
+        W[n, cols] = (0.7 * mag * (1 + g.random(cols.size)) * g.choice([-1, 1], cols.size)).astype(np.float32)
+    X = g.standard_normal((K, M)).astype(np.float32)
+    if bits == 2:
+        np.maximum(X, 0, out=X)
+    step = np.float32(0.75)
+    layer = b.apb_compress(torch.from_numpy(W).cuda(), 0.2)
+    assert b.apb_forward_kernel_name(layer, M, bits).endswith("true>") and b.apb_layer_export_steps(layer)["windows"] == 2
+    Xd = torch.from_numpy(X).cuda()
+    Y = b.apb_forward(layer, b.apb_quantize_acts(Xd, bits, float(step)), M, bits, float(step))
+    assert torch.equal(b.apb_quantize_forward(layer, Xd, bits, float(step)), Y)
+    layer.free()
+    check(b, W, np.float32(0.2), X, bits, step, "several windows")
+
+
 def test_empty_rows_and_very_uneven_rows(b):
     g = np.random.default_rng(31)
     N, K, M = 384, 700, 90
