@@ -65,10 +65,15 @@ __global__ __launch_bounds__(kBlock) void k_row_valsum(const int32_t* __restrict
     if (lane == 0) valsum[n] = sum;
 }
 
+// (It also sets the range of k_residual_range, which follows it, to nothing.)
 __global__ __launch_bounds__(kBlock) void k_rows_sign(const uint32_t* __restrict__ sign, int N, int Kw, int ksteps, long long words,
-                                                      uint32_t* __restrict__ out) {
+                                                      uint32_t* __restrict__ out, int32_t* __restrict__ range) {
     const long long t = (long long)blockIdx.x * kBlock + threadIdx.x;
     if (t >= words) return;
+    if (t == 0) {
+        range[0] = INT_MAX;
+        range[1] = INT_MIN;
+    }
     const int lane = (int)(t & 63), g = lane >> 4;
     const long long block = t >> 6;
     const long long n = block / ksteps * 16 + (lane & 15);
@@ -271,14 +276,11 @@ int build_rows_layer(LayerDev& d, int32_t* found, hipStream_t s) {
     const int tiles = 2 * ((d.N + 31) / 32), quads = 2 * tiles;
     const long long words = (long long)tiles * d.rows_ksteps * 64;
     hipLaunchKernelGGL(k_rows_sign, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, d.sign, d.N, d.Kw, d.rows_ksteps, words,
-                       d.rows_sign);
+                       d.rows_sign, found);
     APB_HIP(hipGetLastError());
 
     // range of the residuals' bits, and from it the lengths of the lists: [0], [1] the range, then [quads][kMaxWindows]
     std::vector<int32_t> h(digit_scratch_words(d.N));
-    h[0] = INT_MAX;
-    h[1] = INT_MIN;
-    APB_HIP(hipMemcpyAsync(found, h.data(), 2 * sizeof(int32_t), hipMemcpyHostToDevice, s));
     if (d.nnz > 0) {
         const long long blocks = (d.nnz + 4 * kBlock - 1) / (4 * kBlock);
         hipLaunchKernelGGL(k_residual_range, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(kBlock), 0, s, d.val, d.nnz, found);
