@@ -130,6 +130,9 @@ inline RowsShape pick_rows_shape(const RowsProblem& q) {
         // 12.1 and 13.1; 256 x 2304 and less: 12.1 and 10.0).
         if (q.packed_out && tiles <= 16 && tiles * ksteps <= 450) h.chunk = tiles;
         h.waves = std::min(8, h.chunk);
+        // Where that leaves compute units to spare, more waves build the tables of a long K (2115 x 2574 in skewed rows, 39
+        // columns: step 17.4 us with two waves, 17.0 with eight; 4096 x 4096, 16 columns: 21.5 and 12.7).
+        while (2 * h.waves <= std::min(8, ksteps) && ct16 * ((tiles + h.chunk - 1) / h.chunk) * 2 * h.waves <= 8 * kComputeUnits) h.waves *= 2;
         return h;
     }
     if (ksteps > 19 && ksteps <= 38) {
